@@ -16,17 +16,6 @@ bool grid_line_supported(int n) {
   }
 }
 
-size_t grid_cols_lds_bytes(int Gy, int ny) {
-  size_t out = 0;
-  (void)with_line(Gy, [&](auto cf) {
-    using CF = decltype(cf);
-    constexpr int L = CF::L, NGRP = 256 / L, NG = (256 + L - 1) / L;
-    out = ((size_t)ny * (NGRP + 1) + (size_t)NG * CF::SPAN) * sizeof(float2);
-    return hipSuccess;
-  });
-  return out;
-}
-
 hipError_t launch_grid_normal(int mode, const Grid2dArgs& a, hipStream_t s) {
   if (a.maps_bf) return launch_grid_normal_bf16(mode, a, s);
   return grid_normal<0>(mode, a, s);
@@ -54,49 +43,75 @@ __global__ __launch_bounds__(64) void k_fft_lines(float2* data, long nlines, con
   }
 }
 
-template <class CF, bool INV>
-__global__ __launch_bounds__(256) void k_fft_cols(float2* data, int ny, int nx, const float2* twt) {
-  constexpr int L = CF::L, NGRP = 256 / L;
-  constexpr int TS = NGRP + 1;
-  extern __shared__ float2 dyn[];
-  float2* tile = dyn;
-  float2* xch = dyn + (size_t)ny * TS;
-  const int g = threadIdx.x / L, lane = threadIdx.x % L;
-  const int x0 = blockIdx.x * NGRP;
-  const size_t plane = (size_t)blockIdx.y * ny * nx;
-  const int ncol = min(NGRP, nx - x0);
-  strip_load(tile, data + plane + x0, ny, NGRP, TS, ncol, nx);
-  __syncthreads();
-  const bool grp = g < NGRP && g < ncol;
-  typename CF::Tw tw;
-  CF::load_tw(tw, twt, lane);
-  float2 v[CF::VMAX];
-#pragma unroll
-  for (int m = 0; m < CF::VA; ++m)
-    v[m] = (grp && CF::inA(lane)) ? tile[CF::posA(lane, m) * TS + g] : make_float2(0.f, 0.f);
-  CF::template forward<INV>(v, xch + g * CF::SPAN, lane, tw);
-  __syncthreads();   // every group has read its column before rows are overwritten
-  if (grp && CF::inB(lane)) {
-#pragma unroll
-    for (int r = 0; r < CF::VB; ++r) tile[CF::posB(lane, r) * TS + g] = v[r];
-  }
-  __syncthreads();
-  strip_store(tile, data + plane + x0, ny, NGRP, TS, ncol, nx);
+// image index of grid index g (line of G points, image of n placed centred
+// on grid index 0), -1 outside
+__device__ __forceinline__ int crop_index(int g, int n, int G) {
+  return g < n / 2 ? g + n / 2 : (g >= G - n / 2 ? g - (G - n / 2) : -1);
 }
 
-template <class CF, bool INV>
-static hipError_t fft_cols(float2* data, long planes, int ny, int nx, const float2* twt, hipStream_t s) {
-  constexpr int L = CF::L, NGRP = 256 / L, NG = (256 + L - 1) / L;
-  const size_t lds = ((size_t)ny * (NGRP + 1) + (size_t)NG * CF::SPAN) * sizeof(float2);
-  if (lds > 160 * 1024) return hipErrorInvalidValue;
-  // allow more than the default 64 KiB of dynamic LDS (once per process,
-  // thread-safe initialisation)
-  static const hipError_t attr = hipFuncSetAttribute((const void*)k_fft_cols<CF, INV>,
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+// Column transforms of planes [rows][Gx], out of place or in place.  CROP: the
+// forward transform reads ny rows, row y being grid row (y - ny/2) mod N and
+// the rest zero, and writes the N grid rows; the inverse one reads N rows and
+// writes those ny.  Otherwise ny = N and rows are grid rows.
+template <class CP, bool INV, bool CROP>
+__global__ __launch_bounds__(CP::THREADS) void k_fft_cols(const float2* in, float2* out, long planes, int ny, int Gx,
+                                                          const float2* __restrict__ twt) {
+  constexpr int LA = CP::LA, VA = CP::VA, N = CP::N;
+  extern __shared__ float2 dyn[];
+  const int S = Gx / kStrip;
+  const long vb = strip_of(blockIdx.x, S * planes);
+  if (vb < 0) return;
+  const int col = threadIdx.x % kStrip, t = threadIdx.x / kStrip;
+  const size_t b = vb / S;
+  const int xc = (int)(vb % S) * kStrip + col;
+  in += b * (CROP && !INV ? ny : N) * Gx + xc;
+  out += b * (CROP && INV ? ny : N) * Gx + xc;
+  float2* ex = dyn + col;
+  if (LA == CP::L || t < LA) {
+    float2 x[VA], tw[VA];
+#pragma unroll
+    for (int m = 0; m < VA; ++m) {
+      const int row = CROP && !INV ? crop_index(t + LA * m, ny, N) : t + LA * m;
+      x[m] = cscale(in[(size_t)(row >= 0 ? row : 0) * Gx], row >= 0 ? 1.f : 0.f);   // unconditional loads
+    }
+#pragma unroll
+    for (int k = 0; k < VA; ++k) tw[k] = twt[t * k];
+    col_a_out<CP, INV, false>(x, tw, ex, t);
+  }
+  __syncthreads();
+  if (VA == CP::L || t < VA) {
+    float2 v[LA];
+    col_b_load<CP>(v, ex, t);
+    dft<LA, INV>(v);
+#pragma unroll
+    for (int r = 0; r < LA; ++r) {
+      const int row = CROP && INV ? crop_index(t + VA * r, ny, N) : t + VA * r;
+      if (row >= 0) out[(size_t)row * Gx] = v[r];
+    }
+  }
+}
+
+template <class CP, bool INV, bool CROP>
+static hipError_t fft_cols(const float2* in, float2* out, long planes, int ny, int Gx, const float2* twt,
+                           hipStream_t s) {
+  static const hipError_t attr = allow_lds((const void*)k_fft_cols<CP, INV, CROP>);
   if (attr != hipSuccess) return attr;
-  dim3 grid((nx + NGRP - 1) / NGRP, (unsigned)planes), block(256);
-  hipLaunchKernelGGL((k_fft_cols<CF, INV>), grid, block, lds, s, data, ny, nx, twt);
+  const dim3 grid(strip_grid(planes * (Gx / kStrip))), block(CP::THREADS);
+  hipLaunchKernelGGL((k_fft_cols<CP, INV, CROP>), grid, block, CP::LDS, s, in, out, planes, ny, Gx, twt);
   return hipGetLastError();
+}
+
+template <bool CROP>
+static hipError_t fft_cols_any(const float2* in, float2* out, long planes, int ny, int Gy, int Gx, bool inverse,
+                               const float2* twt, hipStream_t s) {
+  return with_col(Gy, [&](auto cp) {
+    using CP = decltype(cp);
+    if constexpr (CP::N >= 64 && CP::N != 80 && CP::N != 144) {   // the built grid lengths
+      return inverse ? fft_cols<CP, true, CROP>(in, out, planes, ny, Gx, twt, s)
+                     : fft_cols<CP, false, CROP>(in, out, planes, ny, Gx, twt, s);
+    }
+    return hipErrorInvalidValue;
+  });
 }
 
 hipError_t launch_fft2d(float2* data, long planes, int ny, int nx, bool inverse, const float2* twx,
@@ -111,11 +126,7 @@ hipError_t launch_fft2d(float2* data, long planes, int ny, int nx, bool inverse,
     return hipGetLastError();
   });
   if (e != hipSuccess) return e;
-  return with_line(ny, [&](auto cf) {
-    using CF = decltype(cf);
-    return inverse ? fft_cols<CF, true>(data, planes, ny, nx, twy, s)
-                   : fft_cols<CF, false>(data, planes, ny, nx, twy, s);
-  });
+  return fft_cols_any<false>(data, data, planes, ny, ny, nx, inverse, twy, s);
 }
 
 // ---------------------------------------------------------------- gridding normal operator: image-row passes
@@ -125,11 +136,6 @@ hipError_t launch_fft2d(float2* data, long planes, int ny, int nx, bool inverse,
 // back after the inverse transform.  So the row transforms run on the ny
 // image rows only, kept compactly ([K][ny][Gx], row y), and the column
 // transforms read (forward) or write (inverse) just those rows of the grid.
-
-// image index of grid index g (line of G points, image of n), -1 outside
-__device__ __forceinline__ int crop_index(int g, int n, int G) {
-  return g < n / 2 ? g + n / 2 : (g >= G - n / 2 ? g - (G - n / 2) : -1);
-}
 
 // forward: out[b][y] = FFT_Gx of the grid row of image row y, which holds
 // S_c x[b] dy dx scale at columns (x - nx/2) mod Gx.  inverse: the inverse
@@ -193,50 +199,6 @@ __global__ __launch_bounds__(64) void k_kbn_rows(const float2* __restrict__ in, 
   }
 }
 
-// Column transforms of B planes between the compact image rows and the full
-// grid: forward reads in[b] = [ny][Gx] (image row y is grid row (y - ny/2)
-// mod Gy, zero elsewhere) and writes out[b] = [Gy][Gx]; inverse reads all Gy
-// rows of in[b] and writes only the image rows, out[b] = [ny][Gx].  The strip
-// tile doubles as the groups' exchange regions once every group holds its
-// column in registers.
-template <class CF, bool INV>
-__global__ __launch_bounds__(256) void k_fft_cols_crop(const float2* __restrict__ in, float2* __restrict__ out,
-                                                       int ny, int Gx, const float2* __restrict__ twt) {
-  constexpr int L = CF::L, NGRP = 256 / L, TS = NGRP + 1, GY = CF::N;
-  extern __shared__ float2 dyn[];
-  float2* tile = dyn;
-  const int g = threadIdx.x / L, lane = threadIdx.x % L;
-  const int x0 = blockIdx.x * NGRP;
-  const size_t b = blockIdx.y;
-  const int ncol = min(NGRP, Gx - x0);
-  const int rows_in = INV ? GY : ny, rows_out = INV ? ny : GY;
-  strip_load(tile, in + b * rows_in * Gx + x0, rows_in, NGRP, TS, ncol, Gx);
-  __syncthreads();
-  const bool grp = g < NGRP && g < ncol;
-  typename CF::Tw tw;
-  CF::load_tw(tw, twt, lane);
-  float2 v[CF::VMAX];
-#pragma unroll
-  for (int m = 0; m < CF::VA; ++m) {
-    const int gy = CF::posA(lane, m);
-    const int row = INV ? gy : crop_index(gy, ny, GY);
-    v[m] = (grp && CF::inA(lane) && row >= 0) ? tile[row * TS + g] : make_float2(0.f, 0.f);
-  }
-  __syncthreads();   // every group holds its column: the tile becomes the exchange regions
-  CF::template forward<INV>(v, dyn + g * CF::SPAN, lane, tw);
-  __syncthreads();   // every transform is done before outputs overwrite the exchange regions
-  if (grp && CF::inB(lane)) {
-#pragma unroll
-    for (int r = 0; r < CF::VB; ++r) {
-      const int gy = CF::posB(lane, r);
-      const int row = INV ? crop_index(gy, ny, GY) : gy;
-      if (row >= 0) tile[row * TS + g] = v[r];
-    }
-  }
-  __syncthreads();
-  strip_store(tile, out + b * rows_out * Gx + x0, rows_out, NGRP, TS, ncol, Gx);
-}
-
 hipError_t launch_kbn_rows(bool inverse, const float2* in, const float2* Sc, const float* dy, const float* dx,
                            float2* out, int K, int ny, int nx, int Gx, float scale, int accumulate,
                            const float2* twx, hipStream_t s) {
@@ -255,27 +217,9 @@ hipError_t launch_kbn_rows(bool inverse, const float2* in, const float2* Sc, con
   });
 }
 
-template <class CF, bool INV>
-static hipError_t cols_crop(const float2* in, float2* out, long planes, int ny, int Gx, const float2* twy,
-                            hipStream_t s) {
-  constexpr int L = CF::L, NGRP = 256 / L, NG = (256 + L - 1) / L;
-  const size_t lds = std::max((size_t)CF::N * (NGRP + 1), (size_t)NG * CF::SPAN) * sizeof(float2);
-  if (lds > 160 * 1024) return hipErrorInvalidValue;
-  static const hipError_t attr = hipFuncSetAttribute((const void*)k_fft_cols_crop<CF, INV>,
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-  if (attr != hipSuccess) return attr;
-  const dim3 grid((unsigned)((Gx + NGRP - 1) / NGRP), (unsigned)planes), block(256);
-  hipLaunchKernelGGL((k_fft_cols_crop<CF, INV>), grid, block, lds, s, in, out, ny, Gx, twy);
-  return hipGetLastError();
-}
-
 hipError_t launch_fft_cols_crop(const float2* in, float2* out, long planes, int ny, int Gy, int Gx, bool inverse,
                                 const float2* twy, hipStream_t s) {
-  return with_line(Gy, [&](auto cf) {
-    using CF = decltype(cf);
-    return inverse ? cols_crop<CF, true>(in, out, planes, ny, Gx, twy, s)
-                   : cols_crop<CF, false>(in, out, planes, ny, Gx, twy, s);
-  });
+  return fft_cols_any<true>(in, out, planes, ny, Gy, Gx, inverse, twy, s);
 }
 
 // ---------------------------------------------------------------- k-space inputs
@@ -406,13 +350,12 @@ hipError_t launch_prep_maps_rowmajor(const float2* maps, const double* linv, flo
   return hipGetLastError();
 }
 
-// w[kx][ky] = mask[ky][kx] * scale (Cartesian 2-D weights, transposed)
+// w[ky][kx] = mask[ky][kx] * scale (Cartesian 2-D weights)
 __global__ void k_mask_weights(const uint8_t* __restrict__ mask, float* __restrict__ w, int ny, int nx,
                                float scale) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= ny * nx) return;
-  const int ky = i / nx, kx = i % nx;
-  w[(size_t)kx * ny + ky] = mask[i] ? scale : 0.f;
+  w[i] = mask[i] ? scale : 0.f;
 }
 
 __global__ void k_quantise_maps(float2* __restrict__ maps, uint32_t* __restrict__ bf, long count, int round_copy) {

@@ -5,7 +5,7 @@
 //   q = lam p + sum_c conj(S_c) . crop( G2^-1( W . G2( pad(S_c . p) ) ) )
 //
 // where G2 is the unnormalised 2-D DFT on a Gy x Gx grid and W a real
-// weight, transposed [Gx][Gy] in memory:
+// weight, [Gy][Gx] in memory:
 //  * Cartesian 2-D mask: Gy x Gx = ny x nx, W = mask / (ny nx), maps folded
 //    with (-1)^(y+x) (the centred DFT is (-1)^((ny+nx)/2) D F D, D = (-1)^(y+x),
 //    so the centred-order mask applies unchanged; Sec. 2.1 Eq. (6));
@@ -18,9 +18,9 @@
 //  rows_fwd  per image row: CG update / probe draw, then per coil S_c p,
 //            zero-pad to Gx, row FFT -> T[k][c][y][Gx] (only the ny
 //            non-zero rows of the padded grid are stored);
-//  cols      per tile of adjacent grid columns of one (k, c) plane, staged
-//            through LDS for coalescing: zero-pad to Gy, column FFT,
-//            times W, inverse column FFT, keep rows < ny;
+//  cols      per strip of 16 grid columns of one (k, c) plane (colpass.h):
+//            zero-pad to Gy, column FFT, times W, inverse column FFT, keep
+//            rows < ny;
 //  rows_inv  per image row: per coil inverse row FFT, crop to nx,
 //            conj(S_c) times it, summed over coils; q written with the FP64
 //            partial dots of the CG step.
@@ -29,6 +29,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "colpass.h"
 #include "fft.h"
 #include "runtime.h"
 
@@ -42,8 +43,6 @@ __device__ __forceinline__ MapElem<ST> map_raw(const Grid2dArgs& a, size_t i) {
   if constexpr (ST >= 1) return a.maps_bf[i];
   else return a.maps[i];
 }
-__device__ __forceinline__ float2 widen(float2 v) { return v; }
-__device__ __forceinline__ float2 widen(uint32_t v) { return unpack_bf16x2(v); }
 template <int ST>
 __device__ __forceinline__ float2 map_at(const Grid2dArgs& a, size_t i) { return widen(map_raw<ST>(a, i)); }
 
@@ -285,106 +284,87 @@ __global__ __launch_bounds__(64) void k_rows_fwd(Grid2dArgs a) {
   }
 }
 
-// ---------------------------------------------------------------- column strips
-// Strip of `ncol` (<= ngrp) adjacent columns of one plane to / from an LDS tile
-// [rows][ts].  Loads go out in batches of 8 per thread before any is consumed,
-// so a workgroup keeps 8 x 256 loads in flight instead of one per thread.
-__device__ __forceinline__ void narrow(float2& d, float2 v) { d = v; }
-__device__ __forceinline__ void narrow(uint32_t& d, float2 v) { d = pack_bf16x2(v); }
-
-// E: float2 (complex64 planes) or uint32_t (packed bfloat16 pairs)
-template <class E>
-__device__ __forceinline__ void strip_load(float2* __restrict__ tile, const E* __restrict__ src,
-                                           int rows, int ngrp, int ts, int ncol, long stride) {
-  constexpr int B = 8;
-  const int total = rows * ngrp;
-  for (int i0 = threadIdx.x; i0 < total; i0 += B * 256) {
-    E v[B];
-#pragma unroll
-    for (int u = 0; u < B; ++u) {
-      const int i = i0 + u * 256;
-      const int yy = i / ngrp, j = i % ngrp;
-      v[u] = (i < total && j < ncol) ? src[(size_t)yy * stride + j] : E{};
-    }
-#pragma unroll
-    for (int u = 0; u < B; ++u) {
-      const int i = i0 + u * 256;
-      if (i < total) tile[(i / ngrp) * ts + i % ngrp] = widen(v[u]);
-    }
-  }
-}
-
-template <class E>
-__device__ __forceinline__ void strip_store(const float2* __restrict__ tile, E* __restrict__ dst,
-                                            int rows, int ngrp, int ts, int ncol, long stride) {
-  const int total = rows * ngrp;
-  for (int i = threadIdx.x; i < total; i += 256) {
-    const int yy = i / ngrp, j = i % ngrp;
-    if (j < ncol) narrow(dst[(size_t)yy * stride + j], tile[yy * ts + j]);
-  }
-}
-
 // ---------------------------------------------------------------- column pass
-// One workgroup of 256 lanes: NGRP = 256 / L column groups, one grid column
-// each, adjacent columns of one (k, c) plane.  HALF (the Toeplitz grids,
-// ny = Gy / 2): the input column is zero past its first half and only the
-// first half of the output is kept; both layouts place values m < VA / 2 and
-// r < VB / 2 in the first half, so the zeros and the unused outputs are
-// compile-time facts the compiler folds out of the first and last passes.
-template <class CF, bool TB, bool HALF>
-__global__ __launch_bounds__(256) void k_cols(Grid2dArgs a) {
-  constexpr int L = CF::L, NGRP = 256 / L;
-  constexpr int VA = CF::VA, VB = CF::VB;
-  constexpr int TS = NGRP + 1;  // padded tile row
+// Per column of a (k, c) plane: transform along y, weights, inverse transform,
+// in place.  PAD (the Toeplitz grids, Gy = 2 ny): the column is the first half
+// of a line of 2 ny points, zero past it, and only the first half of the
+// result is kept, so the line is never formed: its even and odd frequencies
+// are two ny-point transforms of the column (times W_{2 ny}^y for the odd
+// ones), and the two inverse transforms add up to the kept half.
+// a.w is [Gy][Gx]; PAD: rows 0..ny-1 the even frequencies, ny..2ny-1 the odd.
+// Bound by the planes' traffic, read and written once each: 2 x 256 padded
+// columns of 256 x 16 coils x 128 probes (4.3 GB) take 1.06 ms, 4.1 TB/s,
+// against 4.4 TB/s for a plain in-place pass over buffers of that size; the
+// staged 512-point transforms this replaces took 1.26 ms with the VALU 93 % busy.
+template <class CP, bool TB, bool PAD>
+__global__ __launch_bounds__(CP::THREADS) void k_cols(Grid2dArgs a) {
+  constexpr int LA = CP::LA, VA = CP::VA, N = CP::N;
   extern __shared__ float2 dyn[];
-  // [ny][TS] tile; once every group holds its column in registers, the same
-  // LDS serves as the NG exchange regions of the transforms
-  float2* tile = dyn;
-  float2* xch = dyn;
-  const int g = threadIdx.x / L, lane = threadIdx.x % L;
-  // Workgroups go to the eight XCDs in turn; workgroup b takes the strip at
-  // v = (b mod 8) * ceil(W / 8) + b / 8 of the order (plane, strip), so each
-  // XCD runs a contiguous run of strips and the cache lines that adjacent
-  // strips share stay in one L2
-  const long S = (a.Gx + NGRP - 1) / NGRP, W = S * (long)a.K * a.nc, per = (W + 7) / 8;
-  const long vb = (long)(blockIdx.x % 8) * per + blockIdx.x / 8;
-  if (vb >= W) return;
-  const int x0 = (int)(vb % S) * NGRP;
-  const size_t plane = (size_t)(vb / S) * a.ny * a.Gx;
-  const int ncol = min(NGRP, a.Gx - x0);
-  if constexpr (TB) strip_load(tile, a.Tb + plane + x0, a.ny, NGRP, TS, ncol, a.Gx);
-  else strip_load(tile, a.T + plane + x0, a.ny, NGRP, TS, ncol, a.Gx);
-  __syncthreads();
-  const bool grp = g < NGRP && g < ncol;
-  const bool inA = CF::inA(lane), inB = CF::inB(lane);
-  typename CF::Tw tw;
-  CF::load_tw(tw, a.twy, lane);
-  float2 v[CF::VMAX];
+  using E = std::conditional_t<TB, uint32_t, float2>;
+  const int S = a.Gx / kStrip;
+  const long vb = strip_of(blockIdx.x, (long)S * a.K * a.nc);
+  if (vb < 0) return;
+  const int col = threadIdx.x % kStrip, t = threadIdx.x / kStrip;
+  const int xc = (int)(vb % S) * kStrip + col;
+  E* __restrict__ pl;
+  if constexpr (TB) pl = a.Tb;
+  else pl = a.T;
+  pl += (size_t)(vb / S) * N * a.Gx + xc;
+  float2* ex = dyn + col;
+  const float2* __restrict__ twy = a.twy;
+  const bool inA = LA == CP::L || t < LA, inB = VA == CP::L || t < VA;
+  E raw[VA];
+  float2 tw[VA];
+  if (inA) {
 #pragma unroll
-  for (int m = 0; m < VA; ++m) {
-    const int yy = CF::posA(lane, m);
-    if (HALF && m >= VA / 2) v[m] = make_float2(0.f, 0.f);
-    else v[m] = (grp && inA && (HALF || yy < a.ny)) ? tile[yy * TS + g] : make_float2(0.f, 0.f);
+    for (int m = 0; m < VA; ++m) raw[m] = pl[(size_t)(t + LA * m) * a.Gx];
+#pragma unroll
+    for (int k = 0; k < VA; ++k) tw[k] = twy[t * k * (PAD ? 2 : 1)];
   }
-  __syncthreads();
-  float2* lds = xch + g * CF::SPAN;
-  CF::template forward<false>(v, lds, lane, tw);
-  const float* __restrict__ wcol = a.w + (size_t)(grp ? x0 + g : 0) * a.Gy;
-  if (inB) {
+  const float* __restrict__ w = a.w + (size_t)t * a.Gx + xc;   // row of layout B's task
+  float2 x[VA], out[VA];
+  if (inA) {
 #pragma unroll
-    for (int r = 0; r < VB; ++r) v[r] = cscale(v[r], wcol[CF::posB(lane, r)]);
+    for (int m = 0; m < VA; ++m) x[m] = widen(raw[m]);
   }
-  CF::template inverse<true>(v, lds, lane, tw);
-  if (grp && inA) {
+  auto weigh = [&](int s) {
+    if (inB) {
+      float wr[LA];
 #pragma unroll
-    for (int m = 0; m < (HALF ? VA / 2 : VA); ++m) {
-      const int yy = CF::posA(lane, m);
-      if (HALF || yy < a.ny) tile[yy * TS + g] = v[m];
+      for (int r = 0; r < LA; ++r) wr[r] = w[(size_t)(s * N + VA * r) * a.Gx];
+      float2 v[LA];
+      col_b_load<CP>(v, ex, t);
+      dft<LA, false>(v);
+#pragma unroll
+      for (int r = 0; r < LA; ++r) v[r] = cscale(v[r], wr[r]);
+      dft<LA, true>(v);
+      col_b_store<CP>(v, ex, t);   // the task's own values: no barrier in between
+    }
+  };
+  if (inA) col_a_out<CP, false, false>(x, tw, ex, t);
+  __syncthreads();
+  weigh(0);
+  __syncthreads();
+  if (inA) col_a_in<CP, true, false>(out, tw, ex, t);
+  if constexpr (PAD) {
+    if (inA) {   // this task's values of the exchange have been read: no barrier
+#pragma unroll
+      for (int k = 0; k < VA; ++k) tw[k] = twy[t * (2 * k + 1)];
+      col_a_out<CP, false, true>(x, tw, ex, t);
+    }
+    __syncthreads();
+    weigh(1);
+    __syncthreads();
+    if (inA) {
+      col_a_in<CP, true, true>(x, tw, ex, t);
+#pragma unroll
+      for (int m = 0; m < VA; ++m) out[m] = cadd(out[m], x[m]);
     }
   }
-  __syncthreads();
-  if constexpr (TB) strip_store(tile, a.Tb + plane + x0, a.ny, NGRP, TS, ncol, a.Gx);
-  else strip_store(tile, a.T + plane + x0, a.ny, NGRP, TS, ncol, a.Gx);
+  if (inA) {
+#pragma unroll
+    for (int m = 0; m < VA; ++m) narrow(pl[(size_t)(t + LA * m) * a.Gx], out[m]);
+  }
 }
 
 // ---------------------------------------------------------------- row pass 2
@@ -658,29 +638,13 @@ static hipError_t rows_inv(int mode, const Grid2dArgs& a, hipStream_t s) {
   return rows_inv_h<CF, ST, false>(mode, a, s);
 }
 
-template <class CF, bool TB, bool HALF>
-static hipError_t cols_launch(const Grid2dArgs& a, size_t lds, hipStream_t s) {
-  constexpr int NGRP = 256 / CF::L;
-  // allow more than the default 64 KiB of dynamic LDS (once per process,
-  // thread-safe initialisation)
-  static const hipError_t attr = hipFuncSetAttribute((const void*)k_cols<CF, TB, HALF>,
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-  if (attr != hipSuccess) return attr;
-  const long W = (long)((a.Gx + NGRP - 1) / NGRP) * a.K * a.nc;
-  dim3 grid((unsigned)(8 * ((W + 7) / 8))), block(256);
-  hipLaunchKernelGGL((k_cols<CF, TB, HALF>), grid, block, lds, s, a);
-  return hipGetLastError();
-}
-
-template <class CF, bool TB>
+template <class CP, bool TB, bool PAD>
 static hipError_t cols(const Grid2dArgs& a, hipStream_t s) {
-  constexpr int L = CF::L, NGRP = 256 / L, NG = (256 + L - 1) / L;
-  const size_t lds = std::max((size_t)a.ny * (NGRP + 1), (size_t)NG * CF::SPAN) * sizeof(float2);
-  if (lds > 160 * 1024) return hipErrorInvalidValue;
-  if constexpr (CF::VA % 2 == 0 && CF::VB % 2 == 0) {
-    if (2 * a.ny == a.Gy) return cols_launch<CF, TB, true>(a, lds, s);
-  }
-  return cols_launch<CF, TB, false>(a, lds, s);
+  static const hipError_t attr = allow_lds((const void*)k_cols<CP, TB, PAD>);
+  if (attr != hipSuccess) return attr;
+  const long W = (long)(a.Gx / kStrip) * a.K * a.nc;
+  hipLaunchKernelGGL((k_cols<CP, TB, PAD>), dim3(strip_grid(W)), dim3(CP::THREADS), CP::LDS, s, a);
+  return hipGetLastError();
 }
 
 
@@ -690,7 +654,17 @@ template <int ST>
 static hipError_t grid_normal(int mode, const Grid2dArgs& a, hipStream_t s) {
   hipError_t e = with_line(a.Gx, [&](auto cf) { return rows_fwd<decltype(cf), ST>(mode, a, s); });
   if (e != hipSuccess) return e;
-  e = with_line(a.Gy, [&](auto cf) { return cols<decltype(cf), ST == 2>(a, s); });
+  e = with_col(a.ny, [&](auto cp) {
+    using CP = decltype(cp);
+    // padded lines have 64 to 768 points, unpadded ones (2-D masks) too
+    if constexpr (CP::N <= 384) {
+      if (a.Gy == 2 * a.ny) return cols<CP, ST == 2, true>(a, s);
+    }
+    if constexpr (CP::N >= 64 && CP::N != 80 && CP::N != 144) {
+      if (a.Gy == a.ny) return cols<CP, ST == 2, false>(a, s);
+    }
+    return hipErrorInvalidValue;
+  });
   if (e != hipSuccess) return e;
   return with_line(a.Gx, [&](auto cf) { return rows_inv<decltype(cf), ST>(mode, a, s); });
 }

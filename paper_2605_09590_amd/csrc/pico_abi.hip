@@ -101,7 +101,7 @@ struct pico_op_s {
   int* gram16_exp = nullptr;  // [nx] block scale exponents
   int* gram16_pexp = nullptr; // [nx][tiles][32] probe scale exponents (kernel scratch)
   float2* twt = nullptr;      // separable path: [ny] twiddles
-  float* w = nullptr;         // grid path: [Gx][Gy] real weights
+  float* w = nullptr;         // grid path: [Gy][Gx] real weights
   float2* twx = nullptr;      // grid path: [Gx] twiddles
   float2* twy = nullptr;      // grid path: [Gy] twiddles
   float2* T = nullptr;        // grid path: [K][nc][ny][Gx]
@@ -758,8 +758,6 @@ pico_status_t validate(const pico_op_desc_t* d) {
     if (!pico::grid_line_supported(f * d->ny) || !pico::grid_line_supported(f * d->nx))
       return fail(PICO_EINVAL, "grid " + std::to_string(f * d->ny) + "x" + std::to_string(f * d->nx) +
                                    " has no built FFT length (64 96 128 160 192 256 288 320 384 512 576 640 768)");
-    if (pico::grid_cols_lds_bytes(f * d->ny, d->ny) > 160 * 1024)
-      return fail(PICO_EINVAL, "column pass does not fit the 160 KiB LDS");
   }
   if (d->cg_iters < 1) return fail(PICO_EINVAL, "cg_iters must be >= 1");
   if (d->probe_tile < 1 || d->probe_tile > 65535) return fail(PICO_EINVAL, "probe_tile must be in 1..65535");
@@ -790,8 +788,6 @@ pico_status_t validate(const pico_op_desc_t* d) {
       if (!pico::grid_line_supported(g))
         return fail(PICO_EINVAL, "gridding length " + std::to_string(g) +
                                      " has no built FFT length (64 96 128 160 192 256 288 320 384 512 576 640 768)");
-    if (pico::grid_cols_lds_bytes(G[0], G[0]) > 160 * 1024)
-      return fail(PICO_EINVAL, "gridding column pass does not fit the 160 KiB LDS");
     if ((double)d->nsamples * d->kb_width * d->kb_width >= 2147483647.0)
       return fail(PICO_EINVAL, "nsamples * kb_width^2 must stay below 2^31");
   }

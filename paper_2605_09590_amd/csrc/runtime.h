@@ -97,7 +97,7 @@ struct Grid2dArgs {
   int ny, nx, nc, K, Gy, Gx;
   const float2* maps;          // [nc][ny][nx] whitened (and sign-folded for Cartesian)
   const uint32_t* maps_bf;     // the same maps as packed bfloat16 pairs, or NULL
-  const float* w;              // [Gx][Gy] real weights
+  const float* w;              // [Gy][Gx] real weights (Toeplitz: even ky first, then odd)
   const float2* twx;           // [Gx] W_Gx^m
   const float2* twy;           // [Gy] W_Gy^m
   float2* T;                   // [K][nc][ny][Gx] row-transformed planes
@@ -119,7 +119,6 @@ struct Grid2dArgs {
 
 bool cart1d_supported(int ny);
 bool grid_line_supported(int n);
-size_t grid_cols_lds_bytes(int Gy, int ny);
 hipError_t launch_grid_normal(int mode, const Grid2dArgs& a, hipStream_t s);
 hipError_t launch_grid_normal_bf16(int mode, const Grid2dArgs& a, hipStream_t s);   // a.maps_bf set
 hipError_t launch_accum_rowmajor(const AccumArgs& a, hipStream_t s);

@@ -4,7 +4,8 @@
 // evaluated separably as a complex matrix product psf = E_y^T E_x with
 // E_y[m][j] = exp(i w_y,m (j - ny + 1)), E_x likewise (a dense contraction
 // over the M samples, taken in chunks of samples); circulant embedding in a 2ny x 2nx grid; its DFT by
-// two more products with DFT matrices; W = Re(DFT) / (4 ny nx), transposed.
+// two more products with DFT matrices; W = Re(DFT) / (4 ny nx), rows in the
+// column pass's order.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -125,13 +126,15 @@ __global__ void k_dft_matrix(z64* __restrict__ F, int G) {
   F[i] = make_double2(c, s);
 }
 
-// w[kx][ky] = Re(Kh[ky][kx]) * scale
+// w[row(ky)][kx] = Re(Kh[ky][kx]) * scale; row: the even ky in order, then the odd
+// ones (the column pass transforms them separately)
 __global__ void k_real_weights(const z64* __restrict__ kh, float* __restrict__ w, int Gy, int Gx,
                                double scale) {
   const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= (long)Gy * Gx) return;
   const int ky = (int)(i / Gx), kx = (int)(i % Gx);
-  w[(size_t)kx * Gy + ky] = (float)(kh[i].x * scale);
+  const int row = (ky & 1) * (Gy / 2) + ky / 2;
+  w[(size_t)row * Gx + kx] = (float)(kh[i].x * scale);
 }
 
 hipError_t zgemm64(const double2* A, const double2* B, double2* C, int Mr, int Nc, int Kd,
