@@ -49,13 +49,14 @@ __device__ __forceinline__ int crop_index(int g, int n, int G) {
   return g < n / 2 ? g + n / 2 : (g >= G - n / 2 ? g - (G - n / 2) : -1);
 }
 
-// Column transforms of planes [rows][Gx], out of place or in place.  CROP: the
-// forward transform reads ny rows, row y being grid row (y - ny/2) mod N and
-// the rest zero, and writes the N grid rows; the inverse one reads N rows and
-// writes those ny.  Otherwise ny = N and rows are grid rows.
+// Column transforms of planes [rows][Gx] (is and os apart), out of place or in
+// place (is = os).  CROP: the forward transform reads ny rows, row y being grid
+// row (y - ny/2) mod N and the rest zero, and writes the N grid rows; the
+// inverse one reads N rows and writes those ny.  Otherwise ny = N and rows are
+// grid rows.
 template <class CP, bool INV, bool CROP>
-__global__ __launch_bounds__(CP::THREADS) void k_fft_cols(const float2* in, float2* out, long planes, int ny, int Gx,
-                                                          const float2* __restrict__ twt) {
+__global__ __launch_bounds__(CP::THREADS) void k_fft_cols(const float2* in, float2* out, long is, long os, long planes,
+                                                          int ny, int Gx, const float2* __restrict__ twt) {
   constexpr int LA = CP::LA, VA = CP::VA, N = CP::N;
   extern __shared__ float2 dyn[];
   const int S = Gx / kStrip;
@@ -64,8 +65,8 @@ __global__ __launch_bounds__(CP::THREADS) void k_fft_cols(const float2* in, floa
   const int col = threadIdx.x % kStrip, t = threadIdx.x / kStrip;
   const size_t b = vb / S;
   const int xc = (int)(vb % S) * kStrip + col;
-  in += b * (CROP && !INV ? ny : N) * Gx + xc;
-  out += b * (CROP && INV ? ny : N) * Gx + xc;
+  in += b * is + xc;
+  out += b * os + xc;
   float2* ex = dyn + col;
   if (LA == CP::L || t < LA) {
     float2 x[VA], tw[VA];
@@ -92,23 +93,23 @@ __global__ __launch_bounds__(CP::THREADS) void k_fft_cols(const float2* in, floa
 }
 
 template <class CP, bool INV, bool CROP>
-static hipError_t fft_cols(const float2* in, float2* out, long planes, int ny, int Gx, const float2* twt,
-                           hipStream_t s) {
+static hipError_t fft_cols(const float2* in, float2* out, long is, long os, long planes, int ny, int Gx,
+                           const float2* twt, hipStream_t s) {
   static const hipError_t attr = allow_lds((const void*)k_fft_cols<CP, INV, CROP>);
   if (attr != hipSuccess) return attr;
   const dim3 grid(strip_grid(planes * (Gx / kStrip))), block(CP::THREADS);
-  hipLaunchKernelGGL((k_fft_cols<CP, INV, CROP>), grid, block, CP::LDS, s, in, out, planes, ny, Gx, twt);
+  hipLaunchKernelGGL((k_fft_cols<CP, INV, CROP>), grid, block, CP::LDS, s, in, out, is, os, planes, ny, Gx, twt);
   return hipGetLastError();
 }
 
 template <bool CROP>
-static hipError_t fft_cols_any(const float2* in, float2* out, long planes, int ny, int Gy, int Gx, bool inverse,
-                               const float2* twt, hipStream_t s) {
+static hipError_t fft_cols_any(const float2* in, float2* out, long is, long os, long planes, int ny, int Gy, int Gx,
+                               bool inverse, const float2* twt, hipStream_t s) {
   return with_col(Gy, [&](auto cp) {
     using CP = decltype(cp);
     if constexpr (CP::N >= 64 && CP::N != 80 && CP::N != 144) {   // the built grid lengths
-      return inverse ? fft_cols<CP, true, CROP>(in, out, planes, ny, Gx, twt, s)
-                     : fft_cols<CP, false, CROP>(in, out, planes, ny, Gx, twt, s);
+      return inverse ? fft_cols<CP, true, CROP>(in, out, is, os, planes, ny, Gx, twt, s)
+                     : fft_cols<CP, false, CROP>(in, out, is, os, planes, ny, Gx, twt, s);
     }
     return hipErrorInvalidValue;
   });
@@ -126,7 +127,8 @@ hipError_t launch_fft2d(float2* data, long planes, int ny, int nx, bool inverse,
     return hipGetLastError();
   });
   if (e != hipSuccess) return e;
-  return fft_cols_any<false>(data, data, planes, ny, ny, nx, inverse, twy, s);
+  const long n = (long)ny * nx;
+  return fft_cols_any<false>(data, data, n, n, planes, ny, ny, nx, inverse, twy, s);
 }
 
 // ---------------------------------------------------------------- gridding normal operator: image-row passes
@@ -137,52 +139,66 @@ hipError_t launch_fft2d(float2* data, long planes, int ny, int nx, bool inverse,
 // image rows only, kept compactly ([K][ny][Gx], row y), and the column
 // transforms read (forward) or write (inverse) just those rows of the grid.
 
-// forward: out[b][y] = FFT_Gx of the grid row of image row y, which holds
-// S_c x[b] dy dx scale at columns (x - nx/2) mod Gx.  inverse: the inverse
-// FFT_Gx of in[b][y] cropped to the image, de-apodised, times conj(S_c) and
-// written (or added, accumulate) to out[b][y][x].  One row per group of L
-// lanes; every load goes out from an in-bounds address.
+// cg coils at a time, planes (b, c) in that order, ps apart.  forward:
+// plane[y] = FFT_Gx of the grid row of image row y, which holds S_c x[b] dy dx
+// scale at columns (x - nx/2) mod Gx; one row of one plane per group of L lanes.
+// inverse: the inverse FFT_Gx of row y of every coil's plane, cropped to the
+// image, times conj(S_c), summed over the coils, de-apodised and written (or
+// added, accumulate) to out[b][y][x]; one image row per group.  Every load goes
+// out from an in-bounds address.
 template <class CF, bool INV>
 __global__ __launch_bounds__(64) void k_kbn_rows(const float2* __restrict__ in, const float2* __restrict__ Sc,
                                                  const float* __restrict__ dy, const float* __restrict__ dx,
-                                                 float2* __restrict__ out, long nlines, int ny, int nx, float scale,
-                                                 int accumulate, const float2* __restrict__ twx) {
+                                                 float2* __restrict__ out, long nlines, int cg, long ps, int ny, int nx,
+                                                 float scale, int accumulate, const float2* __restrict__ twx) {
   constexpr int L = CF::L, G = 64 / L, NG = (64 + L - 1) / L;
   __shared__ float2 lds_all[NG * CF::SPAN];
   const int g = threadIdx.x / L, lane = threadIdx.x % L;
   const long line = (long)blockIdx.x * G + g;
   const bool active = g < G && line < nlines;
   const long ln = active ? line : 0;
+  const long pl = ln / ny;   // plane (forward) or image (inverse)
   const int y = (int)(ln % ny);
   typename CF::Tw tw;
   CF::load_tw(tw, twx, lane);
   const float fy = dy[y] * scale;
-  const float2* sr = Sc + (size_t)y * nx;
+  const size_t n = (size_t)ny * nx;
   float2 v[CF::VMAX];
   if constexpr (!INV) {
-    const float2* xr = in + (size_t)ln * nx;   // image row y of probe ln / ny
+    const float2* sr = Sc + (pl % cg) * n + (size_t)y * nx;
+    const float2* xr = in + (pl / cg) * n + (size_t)y * nx;
 #pragma unroll
     for (int m = 0; m < CF::VA; ++m) {
       const int x = CF::inA(lane) ? crop_index(CF::posA(lane, m), nx, CF::N) : -1;
       const int xs = x >= 0 ? x : 0;
       v[m] = cscale(cmul(sr[xs], xr[xs]), x >= 0 ? fy * dx[xs] : 0.f);
     }
-  } else {
-    const float2* ir = in + (size_t)ln * CF::N;
-#pragma unroll
-    for (int m = 0; m < CF::VA; ++m) {
-      const bool ok = CF::inA(lane);
-      v[m] = cscale(ir[ok ? CF::posA(lane, m) : 0], ok ? 1.f : 0.f);
-    }
-  }
-  CF::template forward<INV>(v, lds_all + g * CF::SPAN, lane, tw);
-  if (!active || !CF::inB(lane)) return;
-  if constexpr (!INV) {
-    float2* o = out + (size_t)ln * CF::N;
+    CF::template forward<false>(v, lds_all + g * CF::SPAN, lane, tw);
+    if (!active || !CF::inB(lane)) return;
+    float2* o = out + pl * ps + (size_t)y * CF::N;
 #pragma unroll
     for (int r = 0; r < CF::VB; ++r) o[CF::posB(lane, r)] = v[r];
   } else {
-    float2* o = out + (size_t)ln * nx;
+    float2 acc[CF::VMAX];
+#pragma unroll
+    for (int r = 0; r < CF::VB; ++r) acc[r] = make_float2(0.f, 0.f);
+    for (int c = 0; c < cg; ++c) {
+      const float2* ir = in + (pl * cg + c) * ps + (size_t)y * CF::N;
+      const float2* sr = Sc + c * n + (size_t)y * nx;
+#pragma unroll
+      for (int m = 0; m < CF::VA; ++m) {
+        const bool ok = CF::inA(lane);
+        v[m] = cscale(ir[ok ? CF::posA(lane, m) : 0], ok ? 1.f : 0.f);
+      }
+      CF::template forward<true>(v, lds_all + g * CF::SPAN, lane, tw);
+#pragma unroll
+      for (int r = 0; r < CF::VB; ++r) {   // values outside the row are not stored
+        const int x = CF::inB(lane) ? crop_index(CF::posB(lane, r), nx, CF::N) : -1;
+        acc[r] = cadd(acc[r], cmulc(sr[x >= 0 ? x : 0], v[r]));
+      }
+    }
+    if (!active || !CF::inB(lane)) return;
+    float2* o = out + pl * n + (size_t)y * nx;
     float2 prev[CF::VMAX];
 #pragma unroll
     for (int r = 0; r < CF::VB; ++r) {
@@ -192,34 +208,32 @@ __global__ __launch_bounds__(64) void k_kbn_rows(const float2* __restrict__ in, 
 #pragma unroll
     for (int r = 0; r < CF::VB; ++r) {
       const int x = crop_index(CF::posB(lane, r), nx, CF::N);
-      const int xs = x >= 0 ? x : 0;
-      const float2 t = cmulc(sr[xs], cscale(v[r], fy * dx[xs]));
-      if (x >= 0) o[x] = cadd(prev[r], t);
+      if (x >= 0) o[x] = cfma(prev[r], fy * dx[x], acc[r]);
     }
   }
 }
 
 hipError_t launch_kbn_rows(bool inverse, const float2* in, const float2* Sc, const float* dy, const float* dx,
-                           float2* out, int K, int ny, int nx, int Gx, float scale, int accumulate,
+                           float2* out, int K, int cg, long ps, int ny, int nx, int Gx, float scale, int accumulate,
                            const float2* twx, hipStream_t s) {
-  const long nlines = (long)K * ny;
+  const long nlines = (long)K * ny * (inverse ? 1 : cg);
   return with_line(Gx, [&](auto cf) {
     using CF = decltype(cf);
     constexpr int G = 64 / CF::L;
     const dim3 grid((unsigned)((nlines + G - 1) / G)), block(64);
     if (inverse)
-      hipLaunchKernelGGL((k_kbn_rows<CF, true>), grid, block, 0, s, in, Sc, dy, dx, out, nlines, ny, nx, scale,
+      hipLaunchKernelGGL((k_kbn_rows<CF, true>), grid, block, 0, s, in, Sc, dy, dx, out, nlines, cg, ps, ny, nx, scale,
                          accumulate, twx);
     else
-      hipLaunchKernelGGL((k_kbn_rows<CF, false>), grid, block, 0, s, in, Sc, dy, dx, out, nlines, ny, nx, scale,
+      hipLaunchKernelGGL((k_kbn_rows<CF, false>), grid, block, 0, s, in, Sc, dy, dx, out, nlines, cg, ps, ny, nx, scale,
                          accumulate, twx);
     return hipGetLastError();
   });
 }
 
-hipError_t launch_fft_cols_crop(const float2* in, float2* out, long planes, int ny, int Gy, int Gx, bool inverse,
-                                const float2* twy, hipStream_t s) {
-  return fft_cols_any<true>(in, out, planes, ny, Gy, Gx, inverse, twy, s);
+hipError_t launch_fft_cols_crop(const float2* in, float2* out, long is, long os, long planes, int ny, int Gy, int Gx,
+                                bool inverse, const float2* twy, hipStream_t s) {
+  return fft_cols_any<true>(in, out, is, os, planes, ny, Gy, Gx, inverse, twy, s);
 }
 
 // ---------------------------------------------------------------- k-space inputs

@@ -668,38 +668,47 @@ hipError_t build_kb(pico_op_t op, const pico_op_desc_t* d, hipStream_t s) {
   o.swy = (float*)part[2];
   o.swx = (float*)part[3];
   o.perm = (int*)part[4];
-  o.bin_ptr = (int*)part[5];
+  o.units = (int2*)part[5];
   o.dy = (float*)part[6];
   o.dx = (float*)part[7];
   o.twx = (float2*)part[8];
   o.twy = (float2*)part[9];
   o.grid = (float2*)part[10];
   o.grid2 = (float2*)part[11];
+  o.tile_ent = (int2*)part[13];
+  o.tile_ptr = (int*)part[14];
+  o.tile_ord = (int*)part[15];
+  o.segs = (int2*)part[16];
+  o.seg0 = (int*)part[17];
   const int nslots = (o.Gy / pico::kKbStencilTile) * (o.Gx / pico::kKbStencilTile);
   o.tile_list = normal ? (int*)part[12] : nullptr;
   o.stencil = normal ? (float*)(part[12] + pico::OffsetArena::round_up((size_t)nslots * 4)) : nullptr;
   std::vector<float> traj((size_t)2 * o.M);
   if ((e = hipMemcpyAsync(traj.data(), d->traj, traj.size() * sizeof(float), hipMemcpyDeviceToHost, s)) != hipSuccess) return e;
   if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
-  std::vector<int> sky0, skx0, perm, bin_ptr;
-  std::vector<float> swy, swx, dy, dx;
-  pico::kb_build_host(traj.data(), o.M, o.W, d->oversamp, o.ny, o.nx, o.Gy, o.Gx, sky0, skx0, swy, swx, perm,
-                      bin_ptr, dy, dx);
+  pico::KbTables t;
+  pico::kb_build_host(traj.data(), o.M, o.W, d->oversamp, o.ny, o.nx, o.Gy, o.Gx, t);
+  o.n_units = (int)t.units.size();
+  o.n_heavy = t.n_heavy;
+  o.n_seg = (int)t.segs.size();
   const std::vector<float2> tx = twiddle_table(o.Gx), ty = twiddle_table(o.Gy);
   auto up = [&](void* dst, const void* src, size_t bytes) {
-    return hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s);
+    return bytes ? hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s) : hipSuccess;
   };
-  if ((e = up(o.sky0, sky0.data(), sky0.size() * 4)) != hipSuccess || (e = up(o.skx0, skx0.data(), skx0.size() * 4)) != hipSuccess ||
-      (e = up(o.swy, swy.data(), swy.size() * 4)) != hipSuccess || (e = up(o.swx, swx.data(), swx.size() * 4)) != hipSuccess ||
-      (e = up(o.perm, perm.data(), perm.size() * 4)) != hipSuccess ||
-      (e = up(o.bin_ptr, bin_ptr.data(), bin_ptr.size() * 4)) != hipSuccess ||
-      (e = up(o.dy, dy.data(), dy.size() * 4)) != hipSuccess || (e = up(o.dx, dx.data(), dx.size() * 4)) != hipSuccess ||
-      (e = up(o.twx, tx.data(), tx.size() * 8)) != hipSuccess || (e = up(o.twy, ty.data(), ty.size() * 8)) != hipSuccess)
+  auto put = [&](auto* dst, const auto& v) { return up(dst, v.data(), v.size() * sizeof(v[0])); };
+  if ((e = put(o.sky0, t.sky0)) != hipSuccess || (e = put(o.skx0, t.skx0)) != hipSuccess ||
+      (e = put(o.swy, t.swy)) != hipSuccess || (e = put(o.swx, t.swx)) != hipSuccess ||
+      (e = put(o.perm, t.perm)) != hipSuccess || (e = put(o.units, t.units)) != hipSuccess ||
+      (e = put(o.dy, t.dy)) != hipSuccess || (e = put(o.dx, t.dx)) != hipSuccess ||
+      (e = put(o.twx, tx)) != hipSuccess || (e = put(o.twy, ty)) != hipSuccess ||
+      (e = put(o.tile_ent, t.tile_ent)) != hipSuccess || (e = put(o.tile_ptr, t.tile_ptr)) != hipSuccess ||
+      (e = put(o.tile_ord, t.tile_ord)) != hipSuccess || (e = put(o.segs, t.segs)) != hipSuccess ||
+      (e = put(o.seg0, t.seg0)) != hipSuccess)
     return e;
   std::vector<int> tile_list;
   std::vector<float> stencil;
   if (normal) {
-    pico::kb_build_stencil(sky0, skx0, swy, swx, o.M, o.W, o.Gy, o.Gx, tile_list, o.n_active, stencil);
+    pico::kb_build_stencil(t.sky0, t.skx0, t.swy, t.swx, o.M, o.W, o.Gy, o.Gx, tile_list, o.n_active, stencil);
     if ((e = up(o.tile_list, tile_list.data(), tile_list.size() * 4)) != hipSuccess ||
         (e = up(o.stencil, stencil.data(), stencil.size() * 4)) != hipSuccess)
       return e;
@@ -720,6 +729,17 @@ bool kb_grid_dims(const pico_op_desc_t* d, int G[2]) {
     G[i] = (int)r;
   }
   return true;
+}
+
+// Room for the data path's grids: the Toeplitz operator's planes (idle while a
+// data pass runs) where they are the larger buffer, so that several coils share
+// a launch, with the gridding tables' own grids for the spread's partial sums;
+// else those grids alone.
+pico::KbScratch kb_scratch(pico_op_t op) {
+  const size_t planes = op->T ? (size_t)op->K * op->nc * op->ny * op->Gx : 0;
+  const size_t grids = (size_t)op->K * op->kb.Gy * op->kb.Gx;
+  if (planes > grids) return {op->T, planes, op->kb.grid, grids};
+  return {op->kb.grid, grids, op->kb.grid2, op->kb.grid2 ? grids : 0};
 }
 
 pico_status_t validate(const pico_op_desc_t* d) {
@@ -1197,8 +1217,9 @@ pico_status_t pico_apply_nufft(pico_op_t op, int32_t adjoint, const void* in, vo
   if (adjoint != 0 && adjoint != 1) return fail(PICO_EINVAL, "adjoint must be 0 or 1");
   hipStream_t s = (hipStream_t)stream;
   op->last_stream = s;
-  if (adjoint) HIP_OR_RETURN(pico::kb_adjoint(op->kb, op->maps, op->nc, k, (const float2*)in, 0, 0, (float2*)out, s));
-  else HIP_OR_RETURN(pico::kb_forward(op->kb, op->maps, op->nc, k, (const float2*)in, (float2*)out, s));
+  const pico::KbScratch sc = kb_scratch(op);
+  if (adjoint) HIP_OR_RETURN(pico::kb_adjoint(op->kb, op->maps, op->nc, k, (const float2*)in, 0, 0, (float2*)out, sc, s));
+  else HIP_OR_RETURN(pico::kb_forward(op->kb, op->maps, op->nc, k, (const float2*)in, (float2*)out, sc, s));
   return PICO_OK;
 }
 
@@ -1291,7 +1312,7 @@ pico_status_t pico_pmr_baseline(pico_op_t op, uint64_t seed, int64_t first, int6
     } else if (op->sampling == PICO_NONCART) {
       // r = A^H n by gridding, CN(0, I) noise on every coil sample (Philox stream 1)
       HIP_OR_RETURN(timed(op, PICO_PROF_OTHER, s, [&] {
-        return pico::kb_adjoint(op->kb, op->maps, op->nc, K, nullptr, seed, f, op->r, s);
+        return pico::kb_adjoint(op->kb, op->maps, op->nc, K, nullptr, seed, f, op->r, kb_scratch(op), s);
       }));
     } else {
       // r = A^H n, white Gaussian k-space noise on the mask (Philox stream 1)

@@ -136,18 +136,19 @@ hipError_t launch_upsample_bilinear(const double* coarse, double* out, int cy, i
 hipError_t launch_power_start_rowmajor(float2* p, int n, hipStream_t s);
 hipError_t launch_fft2d(float2* data, long planes, int ny, int nx, bool inverse, const float2* twx,
                         const float2* twy, hipStream_t s);
-// gridding normal operator passes on the ny image rows of a Gy x Gx grid
-// (image row y at grid row (y - ny/2) mod Gy, column x at (x - nx/2) mod Gx):
-// forward rows: out [K][ny][Gx] = row FFTs of S_c x dy dx scale placed on the
-// grid rows; inverse rows: out [K][ny][nx] (= or +=, accumulate) conj(S_c)
-// dy dx scale times the inverse row FFTs of in [K][ny][Gx], cropped.
-// Column transforms: forward [planes][ny][Gx] (the image rows) -> the full
-// [planes][Gy][Gx]; inverse the full grid -> its image rows [planes][ny][Gx].
+// gridding passes on the ny image rows of Gy x Gx grids (image row y at grid
+// row (y - ny/2) mod Gy, column x at (x - nx/2) mod Gx), cg coils at a time,
+// planes (image, coil) in that order.  Forward rows: plane row y = FFT of
+// S_c x dy dx scale placed on the grid row (planes ps apart); inverse rows: out
+// [K][ny][nx] (= or +=, accumulate) the coil sum of conj(S_c) times the inverse
+// row FFTs, cropped, times dy dx scale.  Column transforms (planes is / os
+// apart, in place when equal): forward the image rows -> the full grid, inverse
+// the full grid -> its image rows.
 hipError_t launch_kbn_rows(bool inverse, const float2* in, const float2* Sc, const float* dy, const float* dx,
-                           float2* out, int K, int ny, int nx, int Gx, float scale, int accumulate,
+                           float2* out, int K, int cg, long ps, int ny, int nx, int Gx, float scale, int accumulate,
                            const float2* twx, hipStream_t s);
-hipError_t launch_fft_cols_crop(const float2* in, float2* out, long planes, int ny, int Gy, int Gx, bool inverse,
-                                const float2* twy, hipStream_t s);
+hipError_t launch_fft_cols_crop(const float2* in, float2* out, long is, long os, long planes, int ny, int Gy, int Gx,
+                                bool inverse, const float2* twy, hipStream_t s);
 hipError_t launch_kspace_in(const float2* src, const double* linv, const uint8_t* mask, float2* out,
                             int B, int nc, int ny, int nx, uint64_t seed, uint64_t first,
                             const uint64_t* tp, uint32_t stream, int dist, float scale, hipStream_t s);
@@ -232,17 +233,22 @@ hipError_t tv_tangent_step(const float2* dz, float2* drA, float2* drB, float2* d
 
 // Kaiser-Bessel gridding NUFFT (non-Cartesian data path)
 // Kaiser-Bessel gridding tables: samples sorted into square bins of
-// kKbTile x kKbTile grid cells by the cell of their first tap, so that every
-// grid tile finds the samples whose footprint reaches it in its own bin and
-// the three bins below / left of it.
+// kKbTile x kKbTile grid cells by the cell of their first tap.  The spread
+// reads, per tile of the same size, the list of the samples whose footprint
+// reaches it (at most 4 M entries in all, since W <= kKbTile); lists of more
+// than kKbSeg entries are cut into segments of that length (at most 8 M / kKbSeg
+// of them).  The interpolation runs units of up to kKbUnit samples of one bin.
 constexpr int kKbTile = 8;
+constexpr int kKbSeg = 256;
+constexpr int kKbUnit = 32;
 // The gridding normal operator applies P^H P (P the interpolation from the
 // grid to the samples) as a precomputed real stencil over (2W - 1)^2 grid
 // offsets, stored for the kKbStencilTile^2-point tiles that any sample's
 // footprint reaches ("active" tiles); the others stay zero.
 constexpr int kKbStencilTile = 16;
 struct KbLayout {
-  static constexpr int kParts = 13;   // sky0 skx0 swy swx perm bin_ptr dy dx twx twy grid grid2 stencil+list
+  // sky0 skx0 swy swx perm units dy dx twx twy grid grid2 stencil+list tile_ent tile_ptr tile_ord segs seg0
+  static constexpr int kParts = 18;
   size_t sizes[kParts];
   size_t bytes_of(size_t i) const;
 };
@@ -257,7 +263,14 @@ struct KbOp {
   int *sky0 = nullptr, *skx0 = nullptr; // [M] first tap cell per axis (mod G), bin order
   float *swy = nullptr, *swx = nullptr; // [M][W] tap weights, bin order
   int* perm = nullptr;                  // [M] sample index of each position in bin order
-  int* bin_ptr = nullptr;               // [nby nbx + 1] first position of each bin
+  int n_units = 0;
+  int2* units = nullptr;                // [n_units] first position and count of each interpolation unit
+  int n_heavy = 0, n_seg = 0;           // cut lists, their segments
+  int2* tile_ent = nullptr;             // (position in bin order, sample) of those that reach each tile
+  int* tile_ptr = nullptr;              // [tiles + 1] first entry of each tile
+  int* tile_ord = nullptr;              // [tiles] the cut ones first
+  int2* segs = nullptr;                 // [n_seg] place in tile_ord and first entry
+  int* seg0 = nullptr;                  // [n_heavy] first segment of each cut tile
   float *dy = nullptr, *dx = nullptr;   // de-apodisation [ny], [nx]
   float2 *twx = nullptr, *twy = nullptr;
   float2* grid = nullptr;               // [K][Gy][Gx]
@@ -270,19 +283,30 @@ struct KbOp {
 };
 double kb_beta(double sigma, int W);
 // host tables in bin order (double precision, stored float32); traj_h [M][2]
-void kb_build_host(const float* traj_h, long M, int W, double sigma, int ny, int nx, int Gy, int Gx,
-                   std::vector<int>& sky0, std::vector<int>& skx0, std::vector<float>& swy,
-                   std::vector<float>& swx, std::vector<int>& perm, std::vector<int>& bin_ptr,
-                   std::vector<float>& dy, std::vector<float>& dx);
+struct KbTables {
+  std::vector<int> sky0, skx0, perm, tile_ptr, tile_ord, seg0;
+  std::vector<int2> units, tile_ent, segs;
+  std::vector<float> swy, swx, dy, dx;
+  int n_heavy = 0;
+};
+void kb_build_host(const float* traj_h, long M, int W, double sigma, int ny, int nx, int Gy, int Gx, KbTables& t);
 // stencil of P^H P in FP64 from the tap tables above (bin order), stored FP32
 // [n_active][(2W - 1)^2][256]; tile_list: active tiles first, in tile order
 void kb_build_stencil(const std::vector<int>& sky0, const std::vector<int>& skx0, const std::vector<float>& swy,
                       const std::vector<float>& swx, long M, int W, int Gy, int Gx, std::vector<int>& tile_list,
                       int& n_active, std::vector<float>& stencil);
+// Scratch of a data pass: buf holds the grids of as many coils as fit (room
+// values, at least K Gy Gx), buf2 (room2 values, may be none) sums of the spread
+struct KbScratch {
+  float2* buf;
+  size_t room;
+  float2* buf2;
+  size_t room2;
+};
 hipError_t kb_adjoint(const KbOp& o, const float2* maps, int nc, int K, const float2* src, uint64_t seed,
-                      uint64_t first, float2* out, hipStream_t s);
+                      uint64_t first, float2* out, const KbScratch& sc, hipStream_t s);
 hipError_t kb_forward(const KbOp& o, const float2* maps, int nc, int K, const float2* x, float2* out,
-                      hipStream_t s);
+                      const KbScratch& sc, hipStream_t s);
 // Gridding normal operator q = (sum_c S_c^H A_c^H A_c S_c + lam) p with the
 // Kaiser-Bessel A_c (interpolation and spread fused per grid tile), in the
 // CG modes and with the partial dots of launch_grid_normal
