@@ -1,6 +1,6 @@
 // Separable Cartesian SENSE: launch of the normal operator (kernels in
-// cart1d_normal.h; cart1d_bf16.hip holds the bfloat16-map instantiation) and
-// the CG building blocks of the column-major layout.
+// cart1d_normal.h, with cart1d_bf16.hip holding the bfloat16-map instantiation,
+// and cart1d_split.h) and the CG building blocks of the column-major layout.
 #include "cart1d_normal.h"
 
 namespace pico {
@@ -15,8 +15,103 @@ bool cart1d_supported(int ny) {
 }
 
 hipError_t launch_cart1d(int mode, const Cart1dArgs& a, hipStream_t s) {
+  if (mode != C1_PMR_RHS) {
+    if (a.split == 2) return launch_cart1d_split2(mode, a, s);
+    if (a.split == 3) return launch_cart1d_split3(mode, a, s);
+    if (unsplit_in_split_kernel(a.ny)) return launch_cart1d_split1(mode, a, s);
+  }
   if (a.maps_bf) return launch_cart1d_bf16(mode, a, s);
   return cart1d_dispatch<false>(mode, a, s);
+}
+
+// ------------------------------------------------------------ split factor
+// The split with the least transform work, at most one partly sampled class
+// (each needs its own copy of the maps): none where every class is full or empty,
+// else one class of ny / S frequencies.  Measured per noise map (12 coils, 128
+// columns, K = 96, CG 6, ms): R = 2 + 24 calibration lines, S = 2, against
+// unsplit 1.50 -> 1.11 (320 points), 1.29 -> 0.94 (256), 2.12 -> 1.54 (384),
+// 0.69 -> 0.59 (128), 0.41 -> 0.41 (64); uniform R = 2 1.50 -> 0.65 (320), 0.41
+// -> 0.22 (64).  R = 3 with calibration lines leaves two classes of S = 3, which
+// ran slower than unsplit (192 points 0.88 -> 1.17, 288 1.51 -> 1.54).
+Fold fold_of(const uint8_t* mask, int ny) {
+  Fold best;
+  for (int s = 1; s <= 3; ++s) {
+    if (ny % s || (s == 3 && ny != 96 && ny != 192 && ny != 288 && ny != 384)) continue;   // built splits
+    Fold f;
+    f.split = s;
+    for (int rho = 0; rho < s; ++rho) {
+      int on = 0;
+      for (int k = rho; k < ny; k += s) on += mask[k] != 0;
+      if (on == ny / s) f.full.push_back(rho);
+      else if (on > 0) f.part.push_back(rho);
+    }
+    // a later split is better if it leaves fewer frequencies to transform
+    if (f.part.size() > 1) continue;
+    if (s == 1 || f.part.size() * (size_t)(ny / s) < best.part.size() * (size_t)(ny / best.split)) best = f;
+  }
+  return best;
+}
+
+// out[col][c][y] = maps[col][c][y] W_ny^{rho y}
+__global__ void k_fold_maps(const float2* __restrict__ maps, float2* __restrict__ out, long total, int ny, int rho) {
+  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= total) return;
+  const int y = (int)(i % ny);
+  double s, c;
+  sincospi(-2.0 * (double)((long)rho * y % ny) / ny, &s, &c);
+  const double re = maps[i].x, im = maps[i].y;
+  out[i] = make_float2((float)(re * c - im * s), (float)(re * s + im * c));
+}
+
+// fully sampled classes (bit rho of full) as one Hermitian block per y' < N = ny / S:
+//   B[t][u] = g[t - u] sum_c conj(S_c[y' + t N]) S_c[y' + u N],
+//   g[d] = (1 / S) sum over the classes of exp(2 pi i rho d / S),
+// out [nx][high, low][S S][N]: per row t the real diagonal, then re and im of B[t][u],
+// u > t
+__global__ void k_fold_gram(const float2* __restrict__ maps, float* __restrict__ out, int nc, int ny, int nx, int S,
+                            unsigned full) {
+  const int N = ny / S, y = blockIdx.x * blockDim.x + threadIdx.x, col = blockIdx.y;
+  if (y >= N) return;
+  const float2* m = maps + (size_t)col * nc * ny + y;
+  float* o = out + (size_t)col * 2 * S * S * N + y;
+  auto put = [&](double v) {   // high word, low word
+    const float hi = (float)v;
+    o[0] = hi;
+    o[(size_t)S * S * N] = (float)(v - (double)hi);
+    o += N;
+  };
+  for (int t = 0; t < S; ++t)
+    for (int u = t; u < S; ++u) {
+      double gr = 0.0, gi = 0.0, re = 0.0, im = 0.0;
+      for (int rho = 0; rho < S; ++rho)
+        if ((full >> rho) & 1u) {
+          double s, c;
+          sincospi(2.0 * rho * (t - u) / S, &s, &c);
+          gr += c / S;
+          gi += s / S;
+        }
+      for (int c = 0; c < nc; ++c) {
+        const float2 a = m[(size_t)c * ny + t * N], b = m[(size_t)c * ny + u * N];
+        re += (double)a.x * b.x + (double)a.y * b.y;
+        im += (double)a.x * b.y - (double)a.y * b.x;
+      }
+      put(gr * re - gi * im);
+      if (u > t) put(gr * im + gi * re);
+    }
+}
+
+hipError_t build_fold(const Fold& f, const float2* maps, int nc, int ny, int nx, float2* fmaps, float* fgram,
+                      hipStream_t s) {
+  const long total = (long)nx * nc * ny;
+  if (f.split > 1)
+    for (int rho : f.part)
+      hipLaunchKernelGGL(k_fold_maps, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, maps, fmaps, total, ny, rho);
+  unsigned full = 0;
+  for (int rho : f.full) full |= 1u << rho;
+  if (full)
+    hipLaunchKernelGGL(k_fold_gram, dim3((ny / f.split + 63) / 64, nx), dim3(64), 0, s, maps, fgram, nc, ny, nx, f.split,
+                       full);
+  return hipGetLastError();
 }
 
 // ------------------------------------------------------------ map preparation

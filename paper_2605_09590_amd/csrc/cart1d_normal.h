@@ -1,5 +1,8 @@
-// Separable Cartesian SENSE normal operator (kernel templates; complex64 and
-// bfloat16 map storage are instantiated in translation units of their own).
+// Separable Cartesian SENSE normal operator on whole columns, and the
+// pseudo-replica right-hand side (kernel templates; complex64 and bfloat16 map
+// storage are instantiated in translation units of their own).  Masks that leave
+// a residue class of the frequencies full or empty take the split kernel instead
+// (cart1d_split.h), which also has the better plans for some unsplit lengths.
 //
 // With a phase-encode mask that is constant along kx, the whitened normal
 // operator M = sum_c S_c^H F^H P F S_c (Sec. 2.1, Eqs. (3), (6)) is block
@@ -334,6 +337,11 @@ template <class CF, bool BF>
 static hipError_t launch_plan(int mode, const Cart1dArgs& a, hipStream_t s) {
   constexpr int G = 64 / CF::L;
   dim3 grid((a.K + G - 1) / G, a.nx), block(64);
+  if constexpr (unsplit_in_split_kernel(CF::N)) {   // the normal operator runs in cart1d_split.h
+    if (mode != C1_PMR_RHS) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_cart1d<CF, C1_PMR_RHS, BF>), grid, block, 0, s, a);
+    return hipGetLastError();
+  }
   switch (mode) {
     case C1_FIRST_PROBE: hipLaunchKernelGGL((k_cart1d<CF, C1_FIRST_PROBE, BF>), grid, block, 0, s, a); break;
     case C1_FIRST_BUF: hipLaunchKernelGGL((k_cart1d<CF, C1_FIRST_BUF, BF>), grid, block, 0, s, a); break;

@@ -93,6 +93,9 @@ struct pico_op_s {
   uint32_t* maps_bf = nullptr;  // bfloat16 storage: the same maps packed (maps then hold the rounded values)
   bool stream_bf = false;     // grid path: row-transformed planes T kept as bfloat16
   float* maskw = nullptr;     // separable path: [ny] mask[k] / ny
+  int split = 1, rho = -1;    // separable path, column transforms: see cart1d_split.h
+  float2* fmaps = nullptr;
+  float* fgram = nullptr;     // NULL: no fully sampled class
   bool use_gram = false;      // separable path: dense per-column blocks on the matrix cores
   float2* gram = nullptr;     // [nx][ny][ny] conj(M_x[i][j]) at [x][j][i]
   double2* gram_c = nullptr;  // [ny] circulant c(d) (build input)
@@ -311,6 +314,10 @@ hipError_t launch_normal(pico_op_t op, int K, int mode, const NormalCall& c, hip
     a.maps = op->maps;
     a.maps_bf = op->maps_bf;
     a.maskw = op->maskw;
+    a.split = op->split;
+    a.rho = op->rho;
+    a.fmaps = op->split > 1 ? op->fmaps : op->maps;
+    a.fgram = op->fgram;
     a.twt = op->twt;
     a.src = c.src;
     a.x = op->x;
@@ -866,6 +873,10 @@ pico_status_t estimate_bytes(const pico_op_desc_t* d, size_t* resident, size_t* 
   if (colmajor) {
     add(ny * 4);
     add(ny * 8);
+    if (!wants_gram(d) && !wants_gram16(d)) {
+      add(n * nc * 8);
+      add(6 * n * 4);
+    }
     if (wants_gram(d)) {
       add(gram_bytes(d->ny, d->nx));
       add(ny * 16);
@@ -1036,6 +1047,18 @@ pico_status_t pico::init_in_arena(const pico_op_desc_t* d, void* stream, pico::D
     if ((e = hipMemcpyAsync(op->twt, tw.data(), ny * sizeof(float2), hipMemcpyHostToDevice, s)) != hipSuccess) return bad(e, "upload");
     if ((e = pico::launch_prep_maps_cart1d((const float2*)d->maps, linv_d, op->maps, nc, ny, nx, s)) != hipSuccess) return bad(e, "prep maps");
     if (op->maps_bf && (e = pico::launch_quantise_maps(op->maps, op->maps_bf, (long)(n * nc), true, s)) != hipSuccess) return bad(e, "bfloat16 maps");
+    if (!wants_gram(d) && !wants_gram16(d)) {
+      // room for any mask: what the split takes follows from the mask, the
+      // byte count from the description alone
+      float* fg = nullptr;
+      if ((e = op->alloc(&op->fmaps, n * nc)) != hipSuccess) return bad(e, "class maps");
+      if ((e = op->alloc(&fg, 6 * n)) != hipSuccess) return bad(e, "class blocks");
+      const pico::Fold f = pico::fold_of(mask_h.data(), ny);
+      op->split = f.split;
+      op->rho = f.part.empty() ? -1 : f.part[0];
+      if (!f.full.empty()) op->fgram = fg;
+      if ((e = pico::build_fold(f, op->maps, nc, ny, nx, op->fmaps, op->fgram, s)) != hipSuccess) return bad(e, "class maps");
+    }
     if (wants_gram(d)) {
       if ((e = op->alloc(&op->gram, pico::gram_bytes(ny, nx) / sizeof(float2))) != hipSuccess) return bad(e, "dense blocks");
       if ((e = op->alloc(&op->gram_c, ny)) != hipSuccess) return bad(e, "dense blocks");

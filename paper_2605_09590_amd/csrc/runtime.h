@@ -42,6 +42,10 @@ struct Cart1dArgs {
   const float2* maps;          // [nx][nc][ny] whitened, (-1)^y folded
   const uint32_t* maps_bf;     // the same maps as packed bfloat16 pairs, or NULL
   const float* maskw;          // [ny] weight mask[k] / ny (0 off the mask)
+  int split;                   // split factor S (cart1d_split.h)
+  int rho;                     // the partly sampled class, or -1
+  const float2* fmaps;         // [nx][nc][ny] maps times W_ny^{rho y}
+  const float* fgram;          // [nx][high, low][S S][ny / S] fully sampled classes, or NULL
   const float2* twt;           // [ny] W_ny^m = exp(-2 pi i m / ny)
   const float2* src;           // input field   (mode dependent)
   float2* x;                   // [K][nx][ny]
@@ -313,6 +317,24 @@ hipError_t kb_forward(const KbOp& o, const float2* maps, int nc, int K, const fl
 hipError_t launch_kb_normal(int mode, const Grid2dArgs& a, const KbOp& o, hipStream_t s);
 hipError_t launch_cart1d(int mode, const Cart1dArgs& a, hipStream_t s);
 hipError_t launch_cart1d_bf16(int mode, const Cart1dArgs& a, hipStream_t s);   // a.maps_bf set
+hipError_t launch_cart1d_split1(int mode, const Cart1dArgs& a, hipStream_t s);
+hipError_t launch_cart1d_split2(int mode, const Cart1dArgs& a, hipStream_t s);
+hipError_t launch_cart1d_split3(int mode, const Cart1dArgs& a, hipStream_t s);
+// lengths whose unsplit columns are faster in the split kernel (S = 1; random
+// masks, 12 coils, 128 columns, K = 96, CG 6: 96 points 1.04 -> 0.61 ms, 256 1.29
+// -> 1.08, 384 2.13 -> 1.92; the others 64 0.42 -> 0.44, 128 0.69 -> 0.71, 160
+// 0.81 -> 0.83, 192 and 288 equal, 320 1.50 -> 1.59, 512 2.23 -> 2.70)
+constexpr bool unsplit_in_split_kernel(int ny) { return ny == 96 || ny == 256 || ny == 384; }
+// split of a phase-encode mask's frequencies into classes k = rho (mod split):
+// the fully and the partly sampled ones
+struct Fold {
+  int split = 1;
+  std::vector<int> full, part;
+};
+Fold fold_of(const uint8_t* mask, int ny);
+// fmaps [nx][nc][ny] (split > 1), fgram [nx][2][split^2][ny / split]
+hipError_t build_fold(const Fold& f, const float2* maps, int nc, int ny, int nx, float2* fmaps, float* fgram,
+                      hipStream_t s);
 // dense per-column normal operator (phase-encode masks, FP32 matrix cores)
 bool gram_supported(int ny);
 size_t gram_bytes(int ny, int nx);
