@@ -21,16 +21,19 @@ namespace pico {
 
 constexpr int kStrip = 16;   // columns per workgroup; every built line length is a multiple of 16
 
-template <int LA_, int VA_>
+// C: the values' type; FP64 strips are half as wide (the same bytes)
+template <int LA_, int VA_, class C = float2>
 struct ColPlan {
   static constexpr int LA = LA_, VA = VA_, N = LA * VA;
   static constexpr int L = LA > VA ? LA : VA;
-  static constexpr int THREADS = kStrip * L;
-  // exchange: Y[a][k] of column j at k KS + 16 a + j; an odd multiple of 128
-  // bytes between consecutive k puts the four tasks of a wavefront on
-  // alternating halves of the LDS banks
-  static constexpr int KS = kStrip * (LA % 2 == 0 ? LA + 1 : LA);
-  static constexpr size_t LDS = (size_t)VA * KS * sizeof(float2);
+  static constexpr int ST = kStrip * (int)sizeof(float2) / (int)sizeof(C);
+  static constexpr int THREADS = ST * L;
+  // exchange: Y[a][k] of column j at k KS + ST a + j; an odd multiple of 128
+  // bytes between consecutive k puts the tasks of a wavefront on alternating
+  // halves of the LDS banks
+  static constexpr int KS = ST * (LA % 2 == 0 ? LA + 1 : LA);
+  static constexpr size_t LDS = (size_t)VA * KS * sizeof(C);
+  using Fp64 = ColPlan<LA, VA, double2>;
 };
 
 // plane values: complex64, or bfloat16 pairs widened and rounded at the edges
@@ -42,9 +45,9 @@ __device__ __forceinline__ void narrow(uint32_t& d, float2 v) { d = pack_bf16x2(
 // Layout A -> exchange: DFT over m of points a + LA m, then W^{a k} (tw).
 // ODD: the points first take the factor W_{2 VA}^m (with tw = W_{2N}^{a (2k+1)}
 // the transform yields the odd frequencies of the zero-padded 2N-point line)
-template <class CP, bool INV, bool ODD>
-__device__ __forceinline__ void col_a_out(const float2 (&x)[CP::VA], const float2 (&tw)[CP::VA], float2* ex, int a) {
-  float2 v[CP::VA];
+template <class CP, bool INV, bool ODD, class C>
+__device__ __forceinline__ void col_a_out(const C (&x)[CP::VA], const C (&tw)[CP::VA], C* ex, int a) {
+  C v[CP::VA];
   static_for<0, CP::VA>([&](auto m) {
     if constexpr (ODD) v[m] = ctwiddle<m, 2 * CP::VA, INV>(x[m]);
     else v[m] = x[m];
@@ -52,19 +55,19 @@ __device__ __forceinline__ void col_a_out(const float2 (&x)[CP::VA], const float
   dft<CP::VA, INV>(v);
 #pragma unroll
   for (int k = 0; k < CP::VA; ++k) {
-    const float2 w = INV ? make_float2(tw[k].x, -tw[k].y) : tw[k];
-    ex[k * CP::KS + kStrip * a] = (ODD || k) ? cmul(v[k], w) : v[k];
+    const C w = INV ? cmake(tw[k].x, -tw[k].y) : tw[k];
+    ex[k * CP::KS + CP::ST * a] = (ODD || k) ? cmul(v[k], w) : v[k];
   }
 }
 
 // exchange -> layout A of the reversed chain (INV names the sign of this transform)
-template <class CP, bool INV, bool ODD>
-__device__ __forceinline__ void col_a_in(float2 (&x)[CP::VA], const float2 (&tw)[CP::VA], const float2* ex, int a) {
-  float2 v[CP::VA];
+template <class CP, bool INV, bool ODD, class C>
+__device__ __forceinline__ void col_a_in(C (&x)[CP::VA], const C (&tw)[CP::VA], const C* ex, int a) {
+  C v[CP::VA];
 #pragma unroll
   for (int k = 0; k < CP::VA; ++k) {
-    const float2 z = ex[k * CP::KS + kStrip * a];
-    const float2 w = INV ? make_float2(tw[k].x, -tw[k].y) : tw[k];
+    const C z = ex[k * CP::KS + CP::ST * a];
+    const C w = INV ? cmake(tw[k].x, -tw[k].y) : tw[k];
     v[k] = (ODD || k) ? cmul(z, w) : z;
   }
   dft<CP::VA, INV>(v);
@@ -74,15 +77,15 @@ __device__ __forceinline__ void col_a_in(float2 (&x)[CP::VA], const float2 (&tw)
   });
 }
 
-template <class CP>
-__device__ __forceinline__ void col_b_load(float2 (&v)[CP::LA], const float2* ex, int k) {
+template <class CP, class C>
+__device__ __forceinline__ void col_b_load(C (&v)[CP::LA], const C* ex, int k) {
 #pragma unroll
-  for (int a = 0; a < CP::LA; ++a) v[a] = ex[k * CP::KS + kStrip * a];
+  for (int a = 0; a < CP::LA; ++a) v[a] = ex[k * CP::KS + CP::ST * a];
 }
-template <class CP>
-__device__ __forceinline__ void col_b_store(const float2 (&v)[CP::LA], float2* ex, int k) {
+template <class CP, class C>
+__device__ __forceinline__ void col_b_store(const C (&v)[CP::LA], C* ex, int k) {
 #pragma unroll
-  for (int a = 0; a < CP::LA; ++a) ex[k * CP::KS + kStrip * a] = v[a];
+  for (int a = 0; a < CP::LA; ++a) ex[k * CP::KS + CP::ST * a] = v[a];
 }
 
 // Strip of workgroup b: workgroups go to the eight XCDs in turn, and workgroup

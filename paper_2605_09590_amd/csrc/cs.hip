@@ -37,13 +37,6 @@ template <class R> __device__ __forceinline__ R wav_g(int k) {
   return (k & 1) ? -wav_h<R>(7 - k) : wav_h<R>(7 - k);
 }
 
-// complex (float2 / double2) accumulate acc + s * v with a real tap s
-__device__ __forceinline__ double2 cfma(double2 acc, double s, double2 a) {
-  return make_double2(fma(s, a.x, acc.x), fma(s, a.y, acc.y));
-}
-template <class C> struct Real;
-template <> struct Real<float2> { using T = float; };
-template <> struct Real<double2> { using T = double; };
 template <class C> __device__ __forceinline__ C czero() { C z; z.x = 0; z.y = 0; return z; }
 
 // Derivative of complex soft-thresholding at the stored coefficient c (FP64,
@@ -58,89 +51,10 @@ __device__ __forceinline__ float2 dsoft_one(float2 d, double2 c, double lam) {
   return make_float2(d.x + f * chy, d.y - f * chx);
 }
 
-// analysis along x of the block [by][bx] of each image
-template <class C>
-__global__ void k_dwt_x(const C* __restrict__ in, C* __restrict__ out, int ny, int nx, int by, int bx) {
-  using R = typename Real<C>::T;
-  const int half = bx / 2;
-  const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= (long)by * half) return;
-  const int y = (int)(t / half), i = (int)(t % half);
-  const size_t img = (size_t)blockIdx.y * ny * nx;
-  const C* row = in + img + (size_t)y * nx;
-  C a = czero<C>(), d = czero<C>();
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    const C v = row[(2 * i + k) % bx];
-    a = cfma(a, wav_h<R>(k), v);
-    d = cfma(d, wav_g<R>(k), v);
-  }
-  out[img + (size_t)y * nx + i] = a;
-  out[img + (size_t)y * nx + half + i] = d;
-}
-
-// analysis along y
-template <class C>
-__global__ void k_dwt_y(const C* __restrict__ in, C* __restrict__ out, int ny, int nx, int by, int bx) {
-  using R = typename Real<C>::T;
-  const int half = by / 2;
-  const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= (long)half * bx) return;
-  const int j = (int)(t / bx), x = (int)(t % bx);
-  const size_t img = (size_t)blockIdx.y * ny * nx;
-  C a = czero<C>(), d = czero<C>();
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    const C v = in[img + (size_t)((2 * j + k) % by) * nx + x];
-    a = cfma(a, wav_h<R>(k), v);
-    d = cfma(d, wav_g<R>(k), v);
-  }
-  out[img + (size_t)j * nx + x] = a;
-  out[img + (size_t)(half + j) * nx + x] = d;
-}
-
-// synthesis along y: x[m] = sum over taps k = m (mod 2) of h[k] a[n] + g[k] d[n],
-// n = ((m - k) / 2) mod (by / 2)
-template <class C>
-__global__ void k_idwt_y(const C* __restrict__ in, C* __restrict__ out, int ny, int nx, int by, int bx) {
-  using R = typename Real<C>::T;
-  const int half = by / 2;
-  const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= (long)by * bx) return;
-  const int m = (int)(t / bx), x = (int)(t % bx);
-  const size_t img = (size_t)blockIdx.y * ny * nx;
-  C acc = czero<C>();
-#pragma unroll
-  for (int kk = 0; kk < 4; ++kk) {
-    const int k = 2 * kk + (m & 1);
-    int n = (m - k) / 2;            // m - k is even
-    n = ((n % half) + half) % half;
-    acc = cfma(acc, wav_h<R>(k), in[img + (size_t)n * nx + x]);
-    acc = cfma(acc, wav_g<R>(k), in[img + (size_t)(half + n) * nx + x]);
-  }
-  out[img + (size_t)m * nx + x] = acc;
-}
-
-// synthesis along x
-template <class C>
-__global__ void k_idwt_x(const C* __restrict__ in, C* __restrict__ out, int ny, int nx, int by, int bx) {
-  using R = typename Real<C>::T;
-  const int half = bx / 2;
-  const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= (long)by * bx) return;
-  const int y = (int)(t / bx), m = (int)(t % bx);
-  const size_t img = (size_t)blockIdx.y * ny * nx;
-  const C* row = in + img + (size_t)y * nx;
-  C acc = czero<C>();
-#pragma unroll
-  for (int kk = 0; kk < 4; ++kk) {
-    const int k = 2 * kk + (m & 1);
-    int n = (m - k) / 2;
-    n = ((n % half) + half) % half;
-    acc = cfma(acc, wav_h<R>(k), row[n]);
-    acc = cfma(acc, wav_g<R>(k), row[half + n]);
-  }
-  out[img + (size_t)y * nx + m] = acc;
+// complex soft threshold
+__device__ __forceinline__ double2 soft_one(double2 v, double lam) {
+  const double a = sqrt(v.x * v.x + v.y * v.y);
+  return cscale(v, a > lam ? 1.0 - lam / a : 0.0);
 }
 
 // One analysis level of the block (by, bx) of each image with both axes in
@@ -150,10 +64,12 @@ __global__ void k_idwt_x(const C* __restrict__ in, C* __restrict__ out, int ny, 
 // so the level reads and writes the block once.  The input block starts at
 // row ri of `in`; the details go to their final places in `out`, the
 // low-low subband to `ll` from row rl (the next level's input, or its final
-// place at the last level).  DSOFT: the soft-threshold derivative at ck is
-// applied to the details as they are written.  GRAD: the input is the FISTA
-// gradient point y - (q - g) / s^2 of three fields (in = y), formed as the
-// tile is loaded.
+// place at the last level).  DET: what happens to the details as they are
+// written: nothing, the soft-threshold derivative at ck (DET_DSOFT), or the soft
+// threshold itself (DET_SOFT; every coefficient first goes to store unless NULL).
+// GRAD: the input is the FISTA gradient point y - (q - g) / s^2 of three fields
+// (in = y), formed as the tile is loaded.
+enum : int { DET_KEEP = 0, DET_DSOFT = 1, DET_SOFT = 2 };
 constexpr int kWT = 16, kWIn = 2 * kWT + 6;
 // v mod n (n > 0), a compare and an add when v is within one period of
 // [0, n) (every index of a tile whose block is at least the tile's span)
@@ -163,12 +79,21 @@ __device__ __forceinline__ int wrapmod(int v, int n) {
   if (v >= n && v < 2 * n) return v - n;
   return ((v % n) + n) % n;
 }
-template <class C, bool DSOFT, bool GRAD>
+template <class C, int DET, bool GRAD>
 __global__ __launch_bounds__(256) void k_dwt2(const C* __restrict__ in, int ri, C* __restrict__ out,
                                               C* __restrict__ ll, int rl, int ny, int nx, int by, int bx,
                                               const double2* __restrict__ ck, double lam, const C* __restrict__ q,
-                                              const C* __restrict__ gr, float inv_s2) {
+                                              const C* __restrict__ gr, typename Real<C>::T inv_s2,
+                                              C* __restrict__ store) {
   using R = typename Real<C>::T;
+  auto detail = [&](C v, size_t i) {   // coefficient i of the image
+    if constexpr (DET == DET_DSOFT) return dsoft_one(v, ck[i], lam);
+    if constexpr (DET == DET_SOFT) {
+      if (store) store[i] = v;
+      return soft_one(v, lam);
+    }
+    return v;
+  };
   __shared__ C sT[kWIn][kWIn + 1];     // input tile
   __shared__ C sX[kWIn][2 * kWT + 1];  // after the x pass: [a | d], 16 each
   const int hy = by / 2, hx = bx / 2;
@@ -209,14 +134,13 @@ __global__ __launch_bounds__(256) void k_dwt2(const C* __restrict__ in, int ri, 
     if (gj < hy && gi < hx) {
       if (c < kWT) {
         ll[img + (size_t)(rl + gj) * nx + gi] = lo;
+        if (DET == DET_SOFT && store && ll == out) store[(size_t)(rl + gj) * nx + gi] = lo;   // the last level
       } else {
         const size_t ilo = (size_t)gj * nx + hx + gi;
-        if constexpr (DSOFT) lo = dsoft_one(lo, ck[ilo], lam);
-        out[img + ilo] = lo;
+        out[img + ilo] = detail(lo, ilo);
       }
       const size_t ihi = (size_t)(hy + gj) * nx + (c < kWT ? 0 : hx) + gi;
-      if constexpr (DSOFT) hi = dsoft_one(hi, ck[ihi], lam);
-      out[img + ihi] = hi;
+      out[img + ihi] = detail(hi, ihi);
     }
   }
 }
@@ -232,7 +156,7 @@ __device__ __forceinline__ int pmod(int v, int n) { return wrapmod(v, n); }
 template <class C, bool MOM>
 __global__ __launch_bounds__(256) void k_idwt2(const C* __restrict__ in, const C* __restrict__ llb, int rl,
                                                C* __restrict__ out, int ro, int ny, int nx, int by, int bx,
-                                               C* __restrict__ y, float theta) {
+                                               C* __restrict__ y, typename Real<C>::T theta) {
   using R = typename Real<C>::T;
   __shared__ C sC[2 * kSW][2 * kSW + 1];   // [y-low | y-high] x [x-low | x-high] windows
   __shared__ C sY[kST][2 * kSW + 1];       // after the y synthesis: 32 rows x [x-low | x-high]
@@ -247,14 +171,13 @@ __global__ __launch_bounds__(256) void k_idwt2(const C* __restrict__ in, const C
   C wv[NIT];
 #pragma unroll
   for (int it = 0; it < NIT; ++it) {
-    const int e = t + 256 * it;
-    if (e < NW) {
-      const int a = e / (2 * kSW), b = e % (2 * kSW);
-      const bool lly = a < kSW, llx = b < kSW;
-      const int ry = lly ? pmod(wy + a, hy) : hy + pmod(wy + a - kSW, hy);
-      const int rx = llx ? pmod(wx + b, hx) : hx + pmod(wx + b - kSW, hx);
-      wv[it] = (lly && llx) ? llb[img + (size_t)(rl + ry) * nx + rx] : in[img + (size_t)ry * nx + rx];
-    }
+    const int e = min(t + 256 * it, NW - 1);   // past the window: its last point again
+    const int a = e / (2 * kSW), b = e % (2 * kSW);
+    const bool lly = a < kSW, llx = b < kSW;
+    const int ry = lly ? pmod(wy + a, hy) : hy + pmod(wy + a - kSW, hy);
+    const int rx = llx ? pmod(wx + b, hx) : hx + pmod(wx + b - kSW, hx);
+    const C* from = (lly && llx) ? llb + (size_t)rl * nx : in;
+    wv[it] = from[img + (size_t)ry * nx + rx];
   }
 #pragma unroll
   for (int it = 0; it < NIT; ++it) {
@@ -297,39 +220,7 @@ __global__ __launch_bounds__(256) void k_idwt2(const C* __restrict__ in, const C
   }
 }
 
-// Psi (forward) or Psi^H (inverse) of K images in place in buf, tmp as scratch
-// levels l0 .. levels - 1 only (the block of level l is (ny >> l) x (nx >> l))
-template <class C>
-static hipError_t wavelet_levels(C* buf, C* tmp, int K, int ny, int nx, int l0, int levels, bool inverse,
-                                 hipStream_t s) {
-  auto grid_for = [&](long work) { return dim3((unsigned)((work + 255) / 256), K); };
-  if (!inverse) {
-    for (int l = l0; l < levels; ++l) {
-      const int by = ny >> l, bx = nx >> l;
-      hipLaunchKernelGGL(k_dwt_x<C>, grid_for((long)by * (bx / 2)), dim3(256), 0, s, buf, tmp, ny, nx, by, bx);
-      hipLaunchKernelGGL(k_dwt_y<C>, grid_for((long)(by / 2) * bx), dim3(256), 0, s, tmp, buf, ny, nx, by, bx);
-    }
-  } else {
-    for (int l = levels - 1; l >= l0; --l) {
-      const int by = ny >> l, bx = nx >> l;
-      hipLaunchKernelGGL(k_idwt_y<C>, grid_for((long)by * bx), dim3(256), 0, s, buf, tmp, ny, nx, by, bx);
-      hipLaunchKernelGGL(k_idwt_x<C>, grid_for((long)by * bx), dim3(256), 0, s, tmp, buf, ny, nx, by, bx);
-    }
-  }
-  return hipGetLastError();
-}
-
-template <class C>
-static hipError_t wavelet(C* buf, C* tmp, int K, int ny, int nx, int levels, bool inverse, hipStream_t s) {
-  return wavelet_levels(buf, tmp, K, ny, nx, 0, levels, inverse, s);
-}
-
 static dim3 grid1(long n, int K = 1) { return dim3((unsigned)((n + 255) / 256), K); }
-
-__device__ __forceinline__ bool is_detail(long i, int nx, int ly, int lx) {
-  const int y = (int)(i / nx), x = (int)(i % nx);
-  return !(y < ly && x < lx);
-}
 
 // z = y - (q - g) * inv_s2 over K images; g has K images or one shared (gK = 0)
 __global__ void k_fista_grad(const float2* __restrict__ y, const float2* __restrict__ q,
@@ -383,66 +274,53 @@ hipError_t launch_fista_grad(const float2* y, const float2* q, const float2* g, 
   return hipGetLastError();
 }
 
-// Tangent analysis of the gradient point z = y - (q - g) * inv_s2 (K images
-// each) into coefficients in dst, the soft-threshold derivative at ck applied
-// to every detail coefficient as it is written.  Each level is one fused
-// pass; level l (block by = ny >> l) reads its input block from scratch rows
-// [by, 2 by) (level 0: z, formed as the tiles load) and writes its low-low
-// subband to scratch rows [by / 2, by), disjoint from its input (the last
-// level: to its final place in dst).
-hipError_t launch_cs_analysis(const float2* y, const float2* q, const float2* g, float inv_s2, float2* scratch,
-                              float2* dst, int K, int ny, int nx, int levels, const double2* ck, double lam,
-                              hipStream_t s) {
+// Prox of the gradient point z = y - (q - g) * inv_s2 (K images each): analysis, the
+// details treated as DET says, synthesis with the FISTA momentum (the image x
+// replaces x_prev in xo and y = x + theta (x - x_prev)).  Each level is one
+// fused pass each way; level l (block by = ny >> l) reads its input block from
+// scratch rows [by, 2 by) (level 0: z, formed as the tiles load), puts its details
+// into dst and its low-low subband into scratch rows [by / 2, by), disjoint from its
+// input (the last level: into its final place in dst).  The synthesis goes the reverse way: low-low from scratch rows [by / 2, by) (last level:
+// dst), block to scratch rows [by, 2 by) (level 0: the image).
+template <class C, int DET>
+static hipError_t prox(C* y, const C* q, const C* g, typename Real<C>::T inv_s2, C* scratch, C* dst, int K, int ny,
+                       int nx, int levels, const double2* ck, double lam, C* store, C* xo, typename Real<C>::T theta,
+                       hipStream_t s) {
   if (levels < 1) return hipErrorInvalidValue;
-  const bool ds = lam != 0.0;
   for (int l = 0; l < levels; ++l) {
     const int by = ny >> l, bx = nx >> l;
     const dim3 grid((unsigned)(((by / 2 + kWT - 1) / kWT) * ((bx / 2 + kWT - 1) / kWT)), (unsigned)K);
     const bool last = l == levels - 1;
-    float2* ll = last ? dst : scratch;
+    C* ll = last ? dst : scratch;
     const int rl = last ? 0 : by / 2;
-    if (l == 0) {
-      if (ds) hipLaunchKernelGGL((k_dwt2<float2, true, true>), grid, dim3(256), 0, s, y, 0, dst, ll, rl, ny, nx, by,
-                                 bx, ck, lam, q, g, inv_s2);
-      else hipLaunchKernelGGL((k_dwt2<float2, false, true>), grid, dim3(256), 0, s, y, 0, dst, ll, rl, ny, nx, by,
-                              bx, ck, lam, q, g, inv_s2);
-    } else {
-      const float2* in = scratch;
-      if (ds) hipLaunchKernelGGL((k_dwt2<float2, true, false>), grid, dim3(256), 0, s, in, by, dst, ll, rl, ny, nx,
-                                 by, bx, ck, lam, q, g, inv_s2);
-      else hipLaunchKernelGGL((k_dwt2<float2, false, false>), grid, dim3(256), 0, s, in, by, dst, ll, rl, ny, nx,
-                              by, bx, ck, lam, q, g, inv_s2);
-    }
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    if (l == 0)
+      hipLaunchKernelGGL((k_dwt2<C, DET, true>), grid, dim3(256), 0, s, (const C*)y, 0, dst, ll, rl, ny, nx, by, bx, ck,
+                         lam, q, g, inv_s2, store);
+    else
+      hipLaunchKernelGGL((k_dwt2<C, DET, false>), grid, dim3(256), 0, s, (const C*)scratch, by, dst, ll, rl, ny, nx, by,
+                         bx, ck, lam, q, g, inv_s2, store);
   }
-  return hipSuccess;
-}
-
-// Tangent synthesis of the coefficients in src (read only) with the FISTA
-// momentum: the image x replaces x_prev in xo and y = x + theta (x - x_prev).
-// Each level is one fused pass; level l (block by = ny >> l) takes its
-// low-low subband from scratch rows [by / 2, by) (the coarsest level: from
-// src) and writes its block to scratch rows [by, 2 by), disjoint from that
-// input (level 0: the image, into xo with the momentum).
-hipError_t launch_cs_synthesis(const float2* src, float2* scratch, int K, int ny, int nx, int levels, float2* xo,
-                               float2* y, float theta, hipStream_t s) {
-  if (levels < 1) return hipErrorInvalidValue;
   for (int l = levels - 1; l >= 0; --l) {
     const int by = ny >> l, bx = nx >> l;
     const dim3 grid((unsigned)(((by + kST - 1) / kST) * ((bx + kST - 1) / kST)), (unsigned)K);
-    const float2* llb = l == levels - 1 ? src : scratch;
+    const C* llb = l == levels - 1 ? dst : scratch;
     const int rl = l == levels - 1 ? 0 : by / 2;
     if (l == 0)
-      hipLaunchKernelGGL((k_idwt2<float2, true>), grid, dim3(256), 0, s, src, llb, rl, xo, 0, ny, nx, by, bx, y,
+      hipLaunchKernelGGL((k_idwt2<C, true>), grid, dim3(256), 0, s, (const C*)dst, llb, rl, xo, 0, ny, nx, by, bx, y,
                          theta);
     else
-      hipLaunchKernelGGL((k_idwt2<float2, false>), grid, dim3(256), 0, s, src, llb, rl, scratch, by, ny, nx, by, bx,
+      hipLaunchKernelGGL((k_idwt2<C, false>), grid, dim3(256), 0, s, (const C*)dst, llb, rl, scratch, by, ny, nx, by, bx,
                          y, theta);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
   }
-  return hipSuccess;
+  return hipGetLastError();
+}
+
+hipError_t launch_cs_prox(float2* y, const float2* q, const float2* g, float inv_s2, float2* scratch, float2* dst, int K,
+                          int ny, int nx, int levels, const double2* ck, double lam, float2* xo, float theta,
+                          hipStream_t s) {
+  if (lam != 0.0)
+    return prox<float2, DET_DSOFT>(y, q, g, inv_s2, scratch, dst, K, ny, nx, levels, ck, lam, nullptr, xo, theta, s);
+  return prox<float2, DET_KEEP>(y, q, g, inv_s2, scratch, dst, K, ny, nx, levels, ck, lam, nullptr, xo, theta, s);
 }
 
 hipError_t launch_momentum(const float2* xn, float2* xo, float2* y, long total, float theta,
@@ -467,27 +345,26 @@ hipError_t launch_fill_zero(float2* a, long total, hipStream_t s) {
 // own trajectory, and the soft-threshold active sets (|c| > lam) decide the
 // tangent map; an FP32 trajectory flips coefficients lying within its rounding
 // of the threshold, so the primal (power method, FISTA, stored c_k) runs in
-// FP64, once per operator.  The normal operator uses the centred orthonormal
-// DFT as dense matrix products: F[k][n] = exp(-2 pi i (k - N/2)(n - N/2) / N) / sqrt(N),
-// symmetric, so A_c y = F_y (S_c y) F_x and A_c^H z = conj(F_y) z conj(F_x).
+// FP64, once per operator (normal operator: cs64.hip).
 
-__global__ void k_centred_dft64(double2* __restrict__ F, int N) {
-  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (long)N * N) return;
-  const long k = i / N - N / 2, m = i % N - N / 2;
-  long p = (k * m) % N;
-  if (p < 0) p += N;
+// W_N^m = exp(-2 pi i m / N), m < N
+__global__ void k_twiddles64(double2* __restrict__ tw, int N) {
+  const int m = blockIdx.x * blockDim.x + threadIdx.x;
+  if (m >= N) return;
   double s, c;
-  sincospi(-2.0 * (double)p / (double)N, &s, &c);
-  const double r = 1.0 / sqrt((double)N);
-  F[i] = make_double2(c * r, s * r);
+  sincospi(-2.0 * (double)m / (double)N, &s, &c);
+  tw[m] = make_double2(c, s);
 }
 
-// S[c] = sum_{d <= c} Linv[c][d] maps[d]   (whitened coil maps, centred order)
+// (-1)^(y+x) of pixel (or k-space point) i
+__device__ __forceinline__ double checker(long i, int nx) { return ((i / nx + i % nx) & 1) ? -1.0 : 1.0; }
+
+// S[c] = (-1)^(y+x) sum_{d <= c} Linv[c][d] maps[d]   (whitened coil maps)
 __global__ void k_prep_maps64(const float2* __restrict__ maps, const double* __restrict__ linv,
-                              double2* __restrict__ S, int nc, long n) {
+                              double2* __restrict__ S, int nc, long n, int nx) {
   const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
+  const double sg = checker(i, nx);
   for (int c = 0; c < nc; ++c) {
     double re = 0.0, im = 0.0;
     for (int d = 0; d <= c; ++d) {
@@ -496,15 +373,16 @@ __global__ void k_prep_maps64(const float2* __restrict__ maps, const double* __r
       re += lr * m.x - li * m.y;
       im += lr * m.y + li * m.x;
     }
-    S[(size_t)c * n + i] = make_double2(re, im);
+    S[(size_t)c * n + i] = make_double2(sg * re, sg * im);
   }
 }
 
-// U[c] = mask * sum_{d <= c} Linv[c][d] kdata[d]   (whitened, sampled k-space)
+// U[c] = (-1)^(ky+kx) mask sum_{d <= c} Linv[c][d] kdata[d]   (whitened, sampled k-space)
 __global__ void k_whiten64(const float2* __restrict__ kd, const double* __restrict__ linv,
-                           const uint8_t* __restrict__ mask, double2* __restrict__ U, int nc, long n) {
+                           const uint8_t* __restrict__ mask, double2* __restrict__ U, int nc, long n, int nx) {
   const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
+  const double sg = checker(i, nx);
   const bool on = mask[i] != 0;
   for (int c = 0; c < nc; ++c) {
     double re = 0.0, im = 0.0;
@@ -514,31 +392,18 @@ __global__ void k_whiten64(const float2* __restrict__ kd, const double* __restri
       re += lr * m.x - li * m.y;
       im += lr * m.y + li * m.x;
     }
-    U[(size_t)c * n + i] = make_double2(re, im);
+    U[(size_t)c * n + i] = make_double2(sg * re, sg * im);
   }
 }
 
-// U[b][c] = S_c y[b]   (batch b = blockIdx.y)
-__global__ void k_mul_maps64(const double2* __restrict__ y, const double2* __restrict__ S,
-                             double2* __restrict__ U, int nc, long n) {
-  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  const int b = blockIdx.y;
-  if (i >= n) return;
-  const double2 v = y[(size_t)b * n + i];
-  double2* Ub = U + (size_t)b * nc * n;
-  for (int c = 0; c < nc; ++c) {
-    const double2 m = S[(size_t)c * n + i];
-    Ub[(size_t)c * n + i] = make_double2(m.x * v.x - m.y * v.y, m.x * v.y + m.y * v.x);
-  }
-}
-
-// U[b][c][i] = mask[i] sigma n, n a CN(0, 1) Philox draw (stream 1, element
-// c n + i, draw first + b): the PMR perturbation of whitened k-space
-__global__ void k_noise64(double2* __restrict__ U, const uint8_t* __restrict__ mask, int nc, long n,
+// U[b][c][i] = (-1)^(ky+kx) mask[i] sigma n, n a CN(0, 1) Philox draw (stream 1,
+// element c n + i, draw first + b): the PMR perturbation of whitened k-space
+__global__ void k_noise64(double2* __restrict__ U, const uint8_t* __restrict__ mask, int nc, long n, int nx,
                           uint64_t seed, uint64_t first, double sigma) {
   const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
   const int b = blockIdx.y;
   if (i >= n) return;
+  sigma *= checker(i, nx);
   for (int c = 0; c < nc; ++c) {
     double2 v = make_double2(0.0, 0.0);
     if (mask[i]) {
@@ -575,28 +440,6 @@ __global__ void k_accum_pmr64(const double2* __restrict__ x, const double2* __re
   sum[i] += s;
   sum_im[i] += si;
   sumsq[i] += ss;
-}
-
-__global__ void k_mask64(double2* __restrict__ U, const uint8_t* __restrict__ mask, int nc, long n) {
-  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n || mask[i]) return;
-  for (int c = 0; c < nc; ++c) U[(size_t)c * n + i] = make_double2(0.0, 0.0);
-}
-
-// out[b] = sum_c conj(S_c) U[b][c]   (batch b = blockIdx.y)
-__global__ void k_combine64(const double2* __restrict__ U, const double2* __restrict__ S,
-                            double2* __restrict__ out, int nc, long n) {
-  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  const int b = blockIdx.y;
-  if (i >= n) return;
-  const double2* Ub = U + (size_t)b * nc * n;
-  double re = 0.0, im = 0.0;
-  for (int c = 0; c < nc; ++c) {
-    const double2 m = S[(size_t)c * n + i], u = Ub[(size_t)c * n + i];
-    re += m.x * u.x + m.y * u.y;
-    im += m.x * u.y - m.y * u.x;
-  }
-  out[(size_t)b * n + i] = make_double2(re, im);
 }
 
 // unit random-phase start of the power method (Philox stream 3, key 0, draw 0)
@@ -649,21 +492,6 @@ __global__ void k_grad64(const double2* __restrict__ y, const double2* __restric
   z[i] = make_double2(y[i].x - (q[i].x - g[i].x) * inv_s2, y[i].y - (q[i].y - g[i].y) * inv_s2);
 }
 
-// c_k stored (when store is given), then detail coefficients soft-thresholded
-// in place; total = B images of img pixels each
-__global__ void k_soft_store64(double2* __restrict__ c, double2* __restrict__ store, long total, long img,
-                               int nx, int ly, int lx, double lam) {
-  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= total) return;
-  const double2 v = c[i];
-  if (store) store[i] = v;
-  if (is_detail(i % img, nx, ly, lx)) {
-    const double a = sqrt(v.x * v.x + v.y * v.y);
-    const double sc = a > lam ? 1.0 - lam / a : 0.0;
-    c[i] = make_double2(v.x * sc, v.y * sc);
-  }
-}
-
 // y = xn + theta (xn - xo); xo = xn
 __global__ void k_momentum64(const double2* __restrict__ xn, double2* __restrict__ xo, double2* __restrict__ y,
                              long n, double theta) {
@@ -692,37 +520,16 @@ __global__ void k_fill_zero64(double2* __restrict__ a, long n) {
 
 hipError_t cs64_setup(Cs64& o, const float2* maps, const double* linv, hipStream_t s) {
   const long n = (long)o.ny * o.nx;
-  hipLaunchKernelGGL(k_centred_dft64, grid1((long)o.ny * o.ny), dim3(256), 0, s, o.Fy, o.ny);
-  hipLaunchKernelGGL(k_centred_dft64, grid1((long)o.nx * o.nx), dim3(256), 0, s, o.Fx, o.nx);
-  hipLaunchKernelGGL(k_prep_maps64, grid1(n), dim3(256), 0, s, maps, linv, o.S, o.nc, n);
+  hipLaunchKernelGGL(k_twiddles64, grid1(o.ny), dim3(256), 0, s, o.twy, o.ny);
+  hipLaunchKernelGGL(k_twiddles64, grid1(o.nx), dim3(256), 0, s, o.twx, o.nx);
+  hipLaunchKernelGGL(k_prep_maps64, grid1(n), dim3(256), 0, s, maps, linv, o.S, o.nc, n, o.nx);
   return hipGetLastError();
-}
-
-// out[b] = sum_c conj(S_c) A_c^H of the k-space held in o.U [B][nc] (overwritten)
-static hipError_t cs64_adjoint_u(const Cs64& o, int B, double2* out, hipStream_t s) {
-  const long n = (long)o.ny * o.nx;
-  const int P = B * o.nc;
-  CS_CHECK(zgemm64(o.Fy, o.U, o.V, o.ny, o.nx, o.ny, 2, 1, s, P, 0, n, n));     // conj(F_y) U_bc
-  CS_CHECK(zgemm64(o.V, o.Fx, o.U, P * o.ny, o.nx, o.nx, 4, 1, s));              // . conj(F_x)
-  hipLaunchKernelGGL(k_combine64, grid1(n, B), dim3(256), 0, s, o.U, o.S, out, o.nc, n);
-  return hipGetLastError();
-}
-
-// q[b] = M y[b] for B images
-hipError_t cs64_normal(const Cs64& o, int B, const double2* y, double2* q, hipStream_t s) {
-  const long n = (long)o.ny * o.nx;
-  const int P = B * o.nc;
-  hipLaunchKernelGGL(k_mul_maps64, grid1(n, B), dim3(256), 0, s, y, o.S, o.U, o.nc, n);
-  CS_CHECK(zgemm64(o.U, o.Fx, o.V, P * o.ny, o.nx, o.nx, 0, 1, s));              // (S_c y) F_x
-  CS_CHECK(zgemm64(o.Fy, o.V, o.U, o.ny, o.nx, o.ny, 0, 1, s, P, 0, n, n));     // F_y .
-  hipLaunchKernelGGL(k_mask64, grid1(n), dim3(256), 0, s, o.U, o.mask, P, n);
-  return cs64_adjoint_u(o, B, q, s);
 }
 
 hipError_t cs64_adjoint_kdata(const Cs64& o, const float2* kdata, const double* linv, double2* out,
                               hipStream_t s) {
   const long n = (long)o.ny * o.nx;
-  hipLaunchKernelGGL(k_whiten64, grid1(n), dim3(256), 0, s, kdata, linv, o.mask, o.U, o.nc, n);
+  hipLaunchKernelGGL(k_whiten64, grid1(n), dim3(256), 0, s, kdata, linv, o.mask, o.U, o.nc, n, o.nx);
   return cs64_adjoint_u(o, 1, out, s);
 }
 
@@ -760,22 +567,21 @@ hipError_t cs64_fista(const Cs64& o, int B, const double2* atb, double s2, doubl
                       const double* theta, bool store, double2* y, double2* x, double2* z,
                       double2* tmp, double2* q, hipStream_t s) {
   const long n = (long)o.ny * o.nx, tot = n * B;
-  const int ly = o.ny >> o.levels, lx = o.nx >> o.levels;
   hipLaunchKernelGGL(k_fill_zero64, grid1(tot), dim3(256), 0, s, y, tot);
   hipLaunchKernelGGL(k_fill_zero64, grid1(tot), dim3(256), 0, s, x, tot);
   for (int k = 1; k <= T; ++k) {
     CS_CHECK(cs64_normal(o, B, y, q, s));
-    hipLaunchKernelGGL(k_grad64, grid1(tot), dim3(256), 0, s, y, q, atb, z, tot, 1.0 / s2);
     if (o.tv_inner > 0) {
+      hipLaunchKernelGGL(k_grad64, grid1(tot), dim3(256), 0, s, y, q, atb, z, tot, 1.0 / s2);
       const size_t off = (size_t)(k - 1) * o.tv_inner * n;
       CS_CHECK(tv64_prox(o, B, z, lam, store ? o.tv_what + off : nullptr, store ? o.tv_invn + off : nullptr, s));
+      hipLaunchKernelGGL(k_momentum64, grid1(tot), dim3(256), 0, s, z, x, y, tot, theta[k - 1]);
     } else {
-      CS_CHECK(wavelet(z, tmp, B, o.ny, o.nx, o.levels, false, s));
-      hipLaunchKernelGGL(k_soft_store64, grid1(tot), dim3(256), 0, s, z,
-                         store ? o.ctraj + (size_t)(k - 1) * n : nullptr, tot, n, o.nx, ly, lx, lam);
-      CS_CHECK(wavelet(z, tmp, B, o.ny, o.nx, o.levels, true, s));
+      // the gradient point forms as the analysis loads, the threshold applies as it
+      // writes, the momentum as the synthesis does
+      CS_CHECK((prox<double2, DET_SOFT>(y, q, atb, 1.0 / s2, tmp, z, B, o.ny, o.nx, o.levels, nullptr, lam,
+                                        store ? o.ctraj + (size_t)(k - 1) * n : nullptr, x, theta[k - 1], s)));
     }
-    hipLaunchKernelGGL(k_momentum64, grid1(tot), dim3(256), 0, s, z, x, y, tot, theta[k - 1]);
   }
   return hipGetLastError();
 }
@@ -787,7 +593,7 @@ hipError_t cs64_pmr(const Cs64& o, int B, const double2* atb0, const double2* x0
                     double2* y, double2* x, double2* z, double2* tmp, double2* q, double* sum,
                     double* sum_im, double* sumsq, hipStream_t s) {
   const long n = (long)o.ny * o.nx;
-  hipLaunchKernelGGL(k_noise64, grid1(n, B), dim3(256), 0, s, o.U, o.mask, o.nc, n, seed, first, sigma);
+  hipLaunchKernelGGL(k_noise64, grid1(n, B), dim3(256), 0, s, o.U, o.mask, o.nc, n, o.nx, seed, first, sigma);
   CS_CHECK(cs64_adjoint_u(o, B, atb, s));                                        // A^H (sigma n_b)
   hipLaunchKernelGGL(k_add_bcast64, grid1(n, B), dim3(256), 0, s, atb, atb0, n);   // + A^H b_w
   CS_CHECK(cs64_fista(o, B, atb, s2, lam, T, theta, false, y, x, z, tmp, q, s));

@@ -29,10 +29,28 @@ __device__ __forceinline__ float2 cscale(float2 a, float s) { return make_float2
 __device__ __forceinline__ float2 cfma(float2 acc, float s, float2 a) {
   return make_float2(fmaf(s, a.x, acc.x), fmaf(s, a.y, acc.y));
 }
+// the same in FP64 (the compressed-sensing primal)
+__device__ __forceinline__ double2 cadd(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
+__device__ __forceinline__ double2 csub(double2 a, double2 b) { return make_double2(a.x - b.x, a.y - b.y); }
+__device__ __forceinline__ double2 cmul(double2 a, double2 b) {
+  return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
+}
+__device__ __forceinline__ double2 cmulc(double2 a, double2 b) {
+  return make_double2(a.x * b.x + a.y * b.y, a.x * b.y - a.y * b.x);
+}
+__device__ __forceinline__ double2 cscale(double2 a, double s) { return make_double2(a.x * s, a.y * s); }
+__device__ __forceinline__ double2 cfma(double2 acc, double s, double2 a) {
+  return make_double2(fma(s, a.x, acc.x), fma(s, a.y, acc.y));
+}
+template <class C> struct Real;
+template <> struct Real<float2> { using T = float; };
+template <> struct Real<double2> { using T = double; };
+__device__ __forceinline__ float2 cmake(float x, float y) { return make_float2(x, y); }
+__device__ __forceinline__ double2 cmake(double x, double y) { return make_double2(x, y); }
 // multiply by -j (forward) or +j (inverse)
-template <bool INV>
-__device__ __forceinline__ float2 mul_mj(float2 a) {
-  return INV ? make_float2(-a.y, a.x) : make_float2(a.y, -a.x);
+template <bool INV, class C>
+__device__ __forceinline__ C mul_mj(C a) {
+  return INV ? cmake(-a.y, a.x) : cmake(a.y, -a.x);
 }
 
 // ---------------------------------------------------------------- bfloat16 storage

@@ -19,45 +19,47 @@
 namespace pico {
 
 // ------------------------------------------------------ in-register DFTs
-template <bool INV>
-__device__ __forceinline__ void dft2(float2& a0, float2& a1) {
-  const float2 t = a0;
+template <bool INV, class C>
+__device__ __forceinline__ void dft2(C& a0, C& a1) {
+  const C t = a0;
   a0 = cadd(t, a1);
   a1 = csub(t, a1);
 }
 
-template <bool INV>
-__device__ __forceinline__ void dft3(float2& a0, float2& a1, float2& a2) {
-  constexpr float h = 0.86602540378443864676f;  // sin(2 pi / 3)
-  const float2 t1 = cadd(a1, a2);
-  const float2 t2 = csub(a1, a2);
-  const float2 b = make_float2(a0.x - 0.5f * t1.x, a0.y - 0.5f * t1.y);
-  const float2 d = mul_mj<INV>(make_float2(h * t2.x, h * t2.y));   // -/+ j h t2
+template <bool INV, class C>
+__device__ __forceinline__ void dft3(C& a0, C& a1, C& a2) {
+  using T = typename Real<C>::T;
+  constexpr T h = (T)0.86602540378443864676, half = (T)0.5;  // sin(2 pi / 3)
+  const C t1 = cadd(a1, a2);
+  const C t2 = csub(a1, a2);
+  const C b = cmake(a0.x - half * t1.x, a0.y - half * t1.y);
+  const C d = mul_mj<INV>(cmake(h * t2.x, h * t2.y));   // -/+ j h t2
   a0 = cadd(a0, t1);
   a1 = cadd(b, d);
   a2 = csub(b, d);
 }
 
-template <bool INV>
-__device__ __forceinline__ void dft4(float2& a0, float2& a1, float2& a2, float2& a3) {
-  const float2 s02 = cadd(a0, a2), d02 = csub(a0, a2);
-  const float2 s13 = cadd(a1, a3), d13 = mul_mj<INV>(csub(a1, a3));
+template <bool INV, class C>
+__device__ __forceinline__ void dft4(C& a0, C& a1, C& a2, C& a3) {
+  const C s02 = cadd(a0, a2), d02 = csub(a0, a2);
+  const C s13 = cadd(a1, a3), d13 = mul_mj<INV>(csub(a1, a3));
   a0 = cadd(s02, s13);
   a2 = csub(s02, s13);
   a1 = cadd(d02, d13);
   a3 = csub(d02, d13);
 }
 
-template <bool INV>
-__device__ __forceinline__ void dft5(float2& a0, float2& a1, float2& a2, float2& a3, float2& a4) {
-  constexpr float c1 = (float)tw_cos(1, 5), c2 = (float)tw_cos(2, 5);
-  constexpr float s1 = (float)tw_sin(1, 5), s2 = (float)tw_sin(2, 5);
-  const float2 t1 = cadd(a1, a4), t2 = cadd(a2, a3);
-  const float2 t3 = csub(a1, a4), t4 = csub(a2, a3);
-  const float2 b1 = make_float2(a0.x + c1 * t1.x + c2 * t2.x, a0.y + c1 * t1.y + c2 * t2.y);
-  const float2 b2 = make_float2(a0.x + c2 * t1.x + c1 * t2.x, a0.y + c2 * t1.y + c1 * t2.y);
-  const float2 d1 = mul_mj<INV>(make_float2(s1 * t3.x + s2 * t4.x, s1 * t3.y + s2 * t4.y));
-  const float2 d2 = mul_mj<INV>(make_float2(s2 * t3.x - s1 * t4.x, s2 * t3.y - s1 * t4.y));
+template <bool INV, class C>
+__device__ __forceinline__ void dft5(C& a0, C& a1, C& a2, C& a3, C& a4) {
+  using T = typename Real<C>::T;
+  constexpr T c1 = (T)tw_cos(1, 5), c2 = (T)tw_cos(2, 5);
+  constexpr T s1 = (T)tw_sin(1, 5), s2 = (T)tw_sin(2, 5);
+  const C t1 = cadd(a1, a4), t2 = cadd(a2, a3);
+  const C t3 = csub(a1, a4), t4 = csub(a2, a3);
+  const C b1 = cmake(a0.x + c1 * t1.x + c2 * t2.x, a0.y + c1 * t1.y + c2 * t2.y);
+  const C b2 = cmake(a0.x + c2 * t1.x + c1 * t2.x, a0.y + c2 * t1.y + c1 * t2.y);
+  const C d1 = mul_mj<INV>(cmake(s1 * t3.x + s2 * t4.x, s1 * t3.y + s2 * t4.y));
+  const C d2 = mul_mj<INV>(cmake(s2 * t3.x - s1 * t4.x, s2 * t3.y - s1 * t4.y));
   a0 = cadd(a0, cadd(t1, t2));
   a1 = cadd(b1, d1);
   a4 = csub(b1, d1);
@@ -66,20 +68,21 @@ __device__ __forceinline__ void dft5(float2& a0, float2& a1, float2& a2, float2&
 }
 
 // multiply by the compile-time twiddle W_R^{m} (sign by direction)
-template <int M, int R, bool INV>
-__device__ __forceinline__ float2 ctwiddle(float2 a) {
+template <int M, int R, bool INV, class C>
+__device__ __forceinline__ C ctwiddle(C a) {
+  using T = typename Real<C>::T;
   constexpr int mm = ((M % R) + R) % R;
   if constexpr (mm == 0) {
     return a;
   } else if constexpr ((4 * mm) % R == 0) {
     constexpr int q = (4 * mm) / R;                 // quarter turns, 1..3
-    if constexpr (q == 2) return make_float2(-a.x, -a.y);
+    if constexpr (q == 2) return cmake(-a.x, -a.y);
     else if constexpr (q == 1) return mul_mj<INV>(a);
     else return mul_mj<!INV>(a);
   } else {
-    constexpr float c = (float)tw_cos(mm, R);
-    constexpr float s = INV ? (float)tw_sin(mm, R) : -(float)tw_sin(mm, R);
-    return cmul(a, make_float2(c, s));
+    constexpr T c = (T)tw_cos(mm, R);
+    constexpr T s = INV ? (T)tw_sin(mm, R) : -(T)tw_sin(mm, R);
+    return cmul(a, cmake(c, s));
   }
 }
 
@@ -107,8 +110,8 @@ constexpr int crt_index(int k1, int k2, int F, int Q) {
 //  - otherwise decimation in time:
 //    X[k1 + Q k2] = sum_{n1<F} W_F^{n1 k2} W_R^{n1 k1} Y_{n1}[k1],
 //    Y_{n1} = DFT_Q(x[n1 + F n2]).
-template <int R, bool INV>
-__device__ __forceinline__ void dft(float2 (&a)[R]) {
+template <int R, bool INV, class C>
+__device__ __forceinline__ void dft(C (&a)[R]) {
   if constexpr (R == 1) {
   } else if constexpr (R == 2) {
     dft2<INV>(a[0], a[1]);
@@ -120,13 +123,13 @@ __device__ __forceinline__ void dft(float2 (&a)[R]) {
     dft5<INV>(a[0], a[1], a[2], a[3], a[4]);
   } else if constexpr (gcd_i(dft_split(R), R / dft_split(R)) == 1) {
     constexpr int F = dft_split(R), Q = R / F;
-    float2 y[F][Q];
+    C y[F][Q];
     static_for<0, F>([&](auto n1) {
       static_for<0, Q>([&](auto n2) { y[n1][n2] = a[(Q * n1 + F * n2) % R]; });
       dft<Q, INV>(y[n1]);
     });
     static_for<0, Q>([&](auto k2) {
-      float2 z[F];
+      C z[F];
       static_for<0, F>([&](auto n1) { z[n1] = y[n1][k2]; });
       dft<F, INV>(z);
       static_for<0, F>([&](auto k1) { a[crt_index(k1, k2, F, Q)] = z[k1]; });
@@ -135,13 +138,13 @@ __device__ __forceinline__ void dft(float2 (&a)[R]) {
     constexpr int F = dft_split(R);
     constexpr int Q = R / F;
     static_assert(F * Q == R, "radix must factor into 2, 3, 4, 5");
-    float2 y[F][Q];
+    C y[F][Q];
     static_for<0, F>([&](auto n1) {
       static_for<0, Q>([&](auto n2) { y[n1][n2] = a[n1 + F * n2]; });
       dft<Q, INV>(y[n1]);
     });
     static_for<0, Q>([&](auto k1) {
-      float2 z[F];
+      C z[F];
       static_for<0, F>([&](auto n1) {
         z[n1] = ctwiddle<n1 * k1, R, INV>(y[n1][k1]);
       });

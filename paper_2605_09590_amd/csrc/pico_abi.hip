@@ -130,7 +130,7 @@ struct pico_op_s {
   double2* ctraj = nullptr;     // [T][ny][nx] stored Psi z_k of the FP64 primal
   float2* xrec = nullptr;       // reconstruction
   std::vector<double> theta64;  // FISTA momentum weights (FP64 primal)
-  pico::Cs64 c64;               // FP64 operator of the primal (maps, DFT matrices)
+  pico::Cs64 c64;               // FP64 operator of the primal (maps, twiddles)
   double2 *atb64 = nullptr, *x64 = nullptr;   // A^H b and x_T in FP64
   // replica workspace of pico_pmr_cs, allocated on its first call
   int pmr_B = 0;
@@ -565,10 +565,8 @@ hipError_t fista_tangent(pico_op_t op, int K, hipStream_t s) {
       // xd = Psi^H D_k(Psi zd): zd formed inside the analysis, coefficients in wB
       // (wA scratch), the synthesis applying the momentum into (x, p) directly
       const double2* ck = op->ctraj + (size_t)(k - 1) * n;
-      if ((e2 = pico::launch_cs_analysis(op->p, op->q, op->r, inv_s2, op->wA, op->wB, K, op->ny, op->nx, op->levels,
-                                         ck, op->cs_lam, s)) != hipSuccess)
-        return e2;
-      return pico::launch_cs_synthesis(op->wB, op->wA, K, op->ny, op->nx, op->levels, op->x, op->p, op->theta[k - 1], s);
+      return pico::launch_cs_prox(op->p, op->q, op->r, inv_s2, op->wA, op->wB, K, op->ny, op->nx, op->levels, ck,
+                                  op->cs_lam, op->x, op->theta[k - 1], s);
     });
     if (e != hipSuccess) return e;
   }
@@ -923,12 +921,12 @@ pico_status_t estimate_bytes(const pico_op_desc_t* d, size_t* resident, size_t* 
       add(n * (size_t)d->fista_iters * 16);
     }
     add(n * 8);
-    add(nc * n * 16);   // FP64 maps, DFT matrices, A^H b, x_T (resident)
-    add(ny * ny * 16);
-    add(nx * nx * 16);
+    add(nc * n * 16);   // FP64 maps, twiddles, A^H b, x_T (resident)
+    add(ny * 16);
+    add(nx * 16);
     add(n * 16);
     add(n * 16);
-    const size_t tmp[] = {nc * n * 16, nc * n * 16, n * 16, n * 16, n * 16, n * 16, 2 * CS64_DOT_BLOCKS * 8,
+    const size_t tmp[] = {nc * n * 16, n * 16, n * 16, n * 16, n * 16, 2 * CS64_DOT_BLOCKS * 8,
                           tv ? 2 * n * 16 : 0, tv ? 2 * n * 16 : 0, tv ? n * 16 : 0};
     for (size_t b : tmp) if (b) add(b);
     for (size_t b : tmp) if (b) sub(b);
@@ -1157,7 +1155,7 @@ pico_status_t pico::init_in_arena(const pico_op_desc_t* d, void* stream, pico::D
       if ((e = op->alloc(&op->ctraj, n * (size_t)op->fista_T)) != hipSuccess) return bad(e, "FISTA trajectory");
     }
     if ((e = op->alloc(&op->xrec, n)) != hipSuccess) return bad(e, "reconstruction");
-    // resident FP64 operator (whitened maps, centred DFT matrices), A^H b and
+    // resident FP64 operator (whitened maps, twiddles), A^H b and
     // x_T: the linearisation point, kept for the replicas of pico_pmr_cs
     pico::Cs64& o = op->c64;
     o.ny = ny;
@@ -1170,15 +1168,14 @@ pico_status_t pico::init_in_arena(const pico_op_desc_t* d, void* stream, pico::D
     o.tv_th = op->tv_th64.data();
     o.tv_what = op->tv_what;
     o.tv_invn = op->tv_invn;
-    if ((e = op->alloc(&o.S, (size_t)nc * n)) != hipSuccess || (e = op->alloc(&o.Fy, (size_t)ny * ny)) != hipSuccess ||
-        (e = op->alloc(&o.Fx, (size_t)nx * nx)) != hipSuccess || (e = op->alloc(&op->atb64, n)) != hipSuccess ||
+    if ((e = op->alloc(&o.S, (size_t)nc * n)) != hipSuccess || (e = op->alloc(&o.twy, ny)) != hipSuccess ||
+        (e = op->alloc(&o.twx, nx)) != hipSuccess || (e = op->alloc(&op->atb64, n)) != hipSuccess ||
         (e = op->alloc(&op->x64, n)) != hipSuccess)
       return bad(e, "FP64 operator");
     double2 *y = nullptr, *z = nullptr, *tmp = nullptr, *q = nullptr;
     double* part = nullptr;
-    if ((e = op->alloc(&o.U, (size_t)nc * n)) != hipSuccess || (e = op->alloc(&o.V, (size_t)nc * n)) != hipSuccess ||
-        (e = op->alloc(&y, n)) != hipSuccess || (e = op->alloc(&z, n)) != hipSuccess ||
-        (e = op->alloc(&tmp, n)) != hipSuccess || (e = op->alloc(&q, n)) != hipSuccess ||
+    if ((e = op->alloc(&o.U, (size_t)nc * n)) != hipSuccess || (e = op->alloc(&y, n)) != hipSuccess ||
+        (e = op->alloc(&z, n)) != hipSuccess || (e = op->alloc(&tmp, n)) != hipSuccess || (e = op->alloc(&q, n)) != hipSuccess ||
         (e = op->alloc(&part, 2 * pico::CS64_DOT_BLOCKS)) != hipSuccess)
       return bad(e, "FP64 primal workspace");
     if (tv && ((e = op->alloc(&o.tv_r, 2 * n)) != hipSuccess || (e = op->alloc(&o.tv_p, 2 * n)) != hipSuccess ||
@@ -1194,10 +1191,10 @@ pico_status_t pico::init_in_arena(const pico_op_desc_t* d, void* stream, pico::D
       return bad(e, "FISTA");
     if ((e = pico::launch_to_f32(op->x64, op->xrec, (long)n, s)) != hipSuccess) return bad(e, "reconstruction");
     if ((e = hipStreamSynchronize(s)) != hipSuccess) return bad(e, "FISTA");
-    for (void* ptr : {(void*)o.U, (void*)o.V, (void*)y, (void*)z, (void*)tmp, (void*)q, (void*)part, (void*)o.tv_r,
+    for (void* ptr : {(void*)o.U, (void*)y, (void*)z, (void*)tmp, (void*)q, (void*)part, (void*)o.tv_r,
                       (void*)o.tv_p, (void*)o.tv_u})
       if (ptr) op->release(ptr);
-    o.U = o.V = nullptr;
+    o.U = nullptr;
     o.tv_r = o.tv_p = o.tv_u = nullptr;
   }
   if ((e = hipStreamSynchronize(s)) != hipSuccess) return bad(e, "init");
@@ -1369,18 +1366,18 @@ pico_status_t pico_pmr_cs(pico_op_t op, uint64_t seed, int64_t first, int64_t nr
     const int B = std::min(op->K, 16);
     hipError_t e;
     const bool tv = op->tv_inner > 0;
-    if ((e = op->alloc(&o.U, (size_t)B * op->nc * n)) != hipSuccess || (e = op->alloc(&o.V, (size_t)B * op->nc * n)) != hipSuccess ||
+    if ((e = op->alloc(&o.U, (size_t)B * op->nc * n)) != hipSuccess ||
         (e = op->alloc(&op->pmr_atb, B * n)) != hipSuccess || (e = op->alloc(&op->pmr_y, B * n)) != hipSuccess ||
         (e = op->alloc(&op->pmr_x, B * n)) != hipSuccess || (e = op->alloc(&op->pmr_z, B * n)) != hipSuccess ||
         (e = op->alloc(&op->pmr_tmp, B * n)) != hipSuccess || (e = op->alloc(&op->pmr_q, B * n)) != hipSuccess ||
         (tv && ((e = op->alloc(&op->pmr_tv_r, 2 * B * n)) != hipSuccess ||
                 (e = op->alloc(&op->pmr_tv_p, 2 * B * n)) != hipSuccess ||
                 (e = op->alloc(&op->pmr_tv_u, B * n)) != hipSuccess))) {
-      for (void* p : {(void*)o.U, (void*)o.V, (void*)op->pmr_atb, (void*)op->pmr_y, (void*)op->pmr_x,
+      for (void* p : {(void*)o.U, (void*)op->pmr_atb, (void*)op->pmr_y, (void*)op->pmr_x,
                       (void*)op->pmr_z, (void*)op->pmr_tmp, (void*)op->pmr_q, (void*)op->pmr_tv_r,
                       (void*)op->pmr_tv_p, (void*)op->pmr_tv_u})
         if (p) op->release(p);
-      o.U = o.V = nullptr;
+      o.U = nullptr;
       op->pmr_atb = op->pmr_y = op->pmr_x = op->pmr_z = op->pmr_tmp = op->pmr_q = nullptr;
       op->pmr_tv_r = op->pmr_tv_p = op->pmr_tv_u = nullptr;
       return fail(e == hipErrorOutOfMemory ? PICO_ENOMEM : PICO_EDEVICE, "PMR workspace");
@@ -1452,7 +1449,7 @@ pico_status_t pico_pmr_cs_noalloc(pico_op_t op, uint64_t seed, int64_t first, in
   const bool tv = op->tv_inner > 0;
   const size_t img = pico::OffsetArena::round_up((size_t)B * n * sizeof(double2));
   const size_t coil = pico::OffsetArena::round_up((size_t)B * op->nc * n * sizeof(double2));
-  const size_t need = 2 * coil + 6 * img + (tv ? 5 * img : 0);
+  const size_t need = 2 * coil + 6 * img + (tv ? 5 * img : 0);   // the documented limit; one coil array of it is spare
   if (need > kNoallocBytes)
     return fail(PICO_EINVAL, "replica workspace of " + std::to_string(need) + " bytes (" + std::to_string(B) +
                                  " replicas of " + std::to_string(op->ny) + "x" + std::to_string(op->nx) + "x" +
@@ -1472,7 +1469,6 @@ pico_status_t pico_pmr_cs_noalloc(pico_op_t op, uint64_t seed, int64_t first, in
     return p;
   };
   o.U = take(coil);
-  o.V = take(coil);
   double2 *atb = take(img), *y = take(img), *x = take(img), *z = take(img), *tmp = take(img), *q = take(img);
   if (tv) {
     o.tv_r = take(2 * img);

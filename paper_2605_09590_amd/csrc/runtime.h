@@ -158,15 +158,13 @@ hipError_t launch_kspace_in(const float2* src, const double* linv, const uint8_t
                             const uint64_t* tp, uint32_t stream, int dist, float scale, hipStream_t s);
 hipError_t launch_coil_combine(const float2* T, const float2* maps, float2* out, int B, int nc,
                                long n, hipStream_t s);
-// CS tangents: analysis of the gradient point y - (q - g) * inv_s2 into dst
-// with the soft-threshold derivative at ck on the details (scratch holds the
-// coarser levels' inputs); synthesis of src (read only; scratch for the
-// coarser levels) with the FISTA momentum into (xo, y)
-hipError_t launch_cs_analysis(const float2* y, const float2* q, const float2* g, float inv_s2, float2* scratch,
-                              float2* dst, int K, int ny, int nx, int levels, const double2* ck, double lam,
-                              hipStream_t s);
-hipError_t launch_cs_synthesis(const float2* src, float2* scratch, int K, int ny, int nx, int levels, float2* xo,
-                               float2* y, float theta, hipStream_t s);
+// CS tangents, one FISTA step after the normal operator: analysis of the gradient
+// point y - (q - g) * inv_s2 (details in dst, coarser levels in scratch) with the
+// soft-threshold derivative at ck on the details, and synthesis with the FISTA
+// momentum into (xo, y)
+hipError_t launch_cs_prox(float2* y, const float2* q, const float2* g, float inv_s2, float2* scratch, float2* dst, int K,
+                          int ny, int nx, int levels, const double2* ck, double lam, float2* xo, float theta,
+                          hipStream_t s);
 hipError_t launch_fista_grad(const float2* y, const float2* q, const float2* g, float2* z, long n, int K,
                              int gK, float inv_s2, hipStream_t s);
 hipError_t launch_momentum(const float2* xn, float2* xo, float2* y, long total, float theta,
@@ -178,23 +176,17 @@ size_t toeplitz_scratch_bytes(long M, int ny, int nx);
 // synchronous on s; scratch: toeplitz_scratch_bytes(M, ny, nx) bytes of device memory
 hipError_t build_toeplitz_weights(const float* traj, long M, int ny, int nx, float* w, void* scratch,
                                   hipStream_t s);
-// complex128 GEMM (row-major; flags 1 transA, 2 conjA, 4 conjB; split-K slices
-// land in C[slice]); batch b offsets A, B, C by b * sA, sB, sC
-hipError_t zgemm64(const double2* A, const double2* B, double2* C, int Mr, int Nc, int Kd,
-                   int flags, int splits, hipStream_t s, int batch = 1, long sA = 0, long sB = 0,
-                   long sC = 0);
 
-// FP64 compressed-sensing primal (2-D Cartesian): the normal operator by dense
-// centred-DFT products, power method, FISTA storing its wavelet coefficients
+// FP64 compressed-sensing primal (2-D Cartesian): normal operator, power method,
+// FISTA storing its wavelet coefficients
 constexpr int CS64_DOT_BLOCKS = 1024;
 struct Cs64 {
   int ny = 0, nx = 0, nc = 0, levels = 0;
-  double2* S = nullptr;         // [nc][ny][nx] whitened coil maps
-  double2* Fy = nullptr;        // [ny][ny] centred orthonormal DFT
-  double2* Fx = nullptr;        // [nx][nx]
+  double2* S = nullptr;         // [nc][ny][nx] whitened coil maps times (-1)^(y+x)
+  double2* twy = nullptr;       // [ny] W_ny^m
+  double2* twx = nullptr;       // [nx]
   const uint8_t* mask = nullptr;  // [ny][nx]
   double2* U = nullptr;         // [B][nc][ny][nx] workspace (B images per call)
-  double2* V = nullptr;         // [B][nc][ny][nx] workspace
   // proximal step: the L1 wavelet threshold (tv_inner = 0) or TV by tv_inner
   // dual fast-gradient-projection steps with momentum weights tv_th (host)
   int tv_inner = 0;
@@ -210,6 +202,7 @@ struct Cs64 {
 };
 hipError_t cs64_setup(Cs64& o, const float2* maps, const double* linv, hipStream_t s);
 hipError_t cs64_normal(const Cs64& o, int B, const double2* y, double2* q, hipStream_t s);
+hipError_t cs64_adjoint_u(const Cs64& o, int B, double2* out, hipStream_t s);
 hipError_t cs64_adjoint_kdata(const Cs64& o, const float2* kdata, const double* linv, double2* out,
                               hipStream_t s);
 hipError_t cs64_power(const Cs64& o, int iters, double2* v, double2* w, double* part_d, double* out,

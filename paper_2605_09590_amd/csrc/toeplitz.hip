@@ -27,19 +27,12 @@ __global__ void k_exp_table(const float* __restrict__ traj, int comp, int d0, in
   out[i] = make_double2(c, s);
 }
 
-// C[z][i][j] = sum_{kk in slice z} op(A)[i][kk] op(B)[kk][j]; op(A) = A (A: [Mr][Kd])
-// or A^T (A: [Kd][Mr]), optionally conjugated; op(B) = B or conj(B), B: [Kd][Nc];
-// row-major complex128; 32x32 tile per block.  flags: 1 transA, 2 conjA, 4 conjB.
-// blockIdx.z = batch * S + slice; batch b offsets A, B, C by b * sA, sB, sC.
+// C[z][i][j] = sum_{kk in slice z} op(A)[i][kk] B[kk][j]; op(A) = A (A: [Mr][Kd])
+// or A^T (A: [Kd][Mr], transA), B: [Kd][Nc]; row-major complex128; 32x32 tile per
+// block, blockIdx.z the slice.
 __global__ __launch_bounds__(256) void k_zgemm(const z64* __restrict__ A, const z64* __restrict__ B,
-                                               z64* __restrict__ C, int Mr, int Nc, int Kd,
-                                               int flags, int kslice, int S, long sA, long sB,
-                                               long sC) {
-  const int transA = flags & 1;
-  const int bz = blockIdx.z / S, sl = blockIdx.z % S;
-  A += bz * sA;
-  B += bz * sB;
-  C += bz * sC;
+                                               z64* __restrict__ C, int Mr, int Nc, int Kd, int transA, int kslice) {
+  const int sl = blockIdx.z;
   __shared__ z64 As[16][33];
   __shared__ z64 Bs[16][33];
   const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
@@ -53,8 +46,6 @@ __global__ __launch_bounds__(256) void k_zgemm(const z64* __restrict__ A, const 
       z64 av = make_double2(0.0, 0.0), bv = make_double2(0.0, 0.0);
       if (gk < kend && gi < Mr) av = transA ? A[(size_t)gk * Mr + gi] : A[(size_t)gi * Kd + gk];
       if (gk < kend && gj < Nc) bv = B[(size_t)gk * Nc + gj];
-      if (flags & 2) av.y = -av.y;
-      if (flags & 4) bv.y = -bv.y;
       As[kk][ii] = av;
       Bs[kk][ii] = bv;
     }
@@ -137,12 +128,12 @@ __global__ void k_real_weights(const z64* __restrict__ kh, float* __restrict__ w
   w[(size_t)row * Gx + kx] = (float)(kh[i].x * scale);
 }
 
-hipError_t zgemm64(const double2* A, const double2* B, double2* C, int Mr, int Nc, int Kd,
-                   int flags, int splits, hipStream_t s, int batch, long sA, long sB, long sC) {
+static hipError_t zgemm64(const double2* A, const double2* B, double2* C, int Mr, int Nc, int Kd, int transA,
+                          int splits, hipStream_t s) {
   const int kslice = ((Kd + splits - 1) / splits + 15) / 16 * 16;
   const int S = (Kd + kslice - 1) / kslice;
-  dim3 grid((Nc + 31) / 32, (Mr + 31) / 32, S * batch), block(256);
-  hipLaunchKernelGGL(k_zgemm, grid, block, 0, s, A, B, C, Mr, Nc, Kd, flags, kslice, S, sA, sB, sC);
+  dim3 grid((Nc + 31) / 32, (Mr + 31) / 32, S), block(256);
+  hipLaunchKernelGGL(k_zgemm, grid, block, 0, s, A, B, C, Mr, Nc, Kd, transA, kslice);
   return hipGetLastError();
 }
 
