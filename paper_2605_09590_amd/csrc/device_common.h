@@ -152,6 +152,13 @@ constexpr double red_angle(long m, long R) {
 constexpr double tw_cos(long m, long R) { return taylor_cos(red_angle(m, R)); }
 constexpr double tw_sin(long m, long R) { return taylor_sin(red_angle(m, R)); }
 
+// LDS traffic between the lanes of one wavefront: the hardware keeps a
+// wave's LDS operations in order, this keeps the compiler from moving them
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // ---------------------------------------------------------------- static_for
 template <int B, int E, typename F>
 __device__ __forceinline__ void static_for(F&& f) {

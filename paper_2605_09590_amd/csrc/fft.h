@@ -247,10 +247,10 @@ __device__ __forceinline__ void fft_pass(float2 (&v)[PL::P], float2* lds, int t,
     }
   }
   if constexpr (!last) {
-    __syncthreads();
+    wave_sync();
 #pragma unroll
     for (int m = 0; m < PL::P; ++m) v[m] = lds[lds_pad(t + T * m)];
-    __syncthreads();
+    wave_sync();
   }
 }
 
@@ -276,7 +276,7 @@ namespace pico {
 // Inverse B -> A is the same chain reversed with conjugate twiddles, so one
 // LDS exchange per transform and both twiddle stages use lane a's own set
 // {W_N^{a k} : 0 < k < VA}.  Lanes that are idle in a step still reach every
-// barrier.
+// sync (the groups of one wavefront: no workgroup barrier).
 template <int LA_, int VA_>
 struct TwoStep {
   static constexpr int LA = LA_, VA = VA_, N = LA * VA;
@@ -316,7 +316,7 @@ struct TwoStep {
         lds[k * STRIDE + lane] = k ? cmul(a[k], w) : a[k];
       }
     }
-    __syncthreads();
+    wave_sync();
     if (inB(lane)) {
       float2 b[LA];
 #pragma unroll
@@ -325,7 +325,7 @@ struct TwoStep {
 #pragma unroll
       for (int r = 0; r < LA; ++r) v[r] = b[r];
     }
-    __syncthreads();
+    wave_sync();
   }
 
   // v[0..LA) in layout B  ->  v[0..VA) in layout A
@@ -339,7 +339,7 @@ struct TwoStep {
 #pragma unroll
       for (int a = 0; a < LA; ++a) lds[lane * STRIDE + a] = b[a];
     }
-    __syncthreads();
+    wave_sync();
     if (inA(lane)) {
       float2 a[VA];
 #pragma unroll
@@ -352,7 +352,7 @@ struct TwoStep {
 #pragma unroll
       for (int m = 0; m < VA; ++m) v[m] = a[m];
     }
-    __syncthreads();
+    wave_sync();
   }
 };
 

@@ -60,11 +60,19 @@ __device__ __forceinline__ float2 map_at(const Grid2dArgs& a, size_t i) { return
 // the counter has drained.  Issued explicitly before the first read of a
 // fetched row: the compiler does not order LDS reads after these loads.
 __device__ __forceinline__ void wait_lds_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }
+// The loads write LDS outside the wavefront's in-order LDS queue: the reads of what
+// they overwrite have to have returned (lgkmcnt 0) before they go out
+__device__ __forceinline__ void wait_lds_reads() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+  __builtin_amdgcn_s_waitcnt(0xC07F);
+  __builtin_amdgcn_wave_barrier();
+}
 
 template <class CF, class E, int GS, class F>
 __device__ __forceinline__ void dma_rows(E* dst, int n, F&& src) {
   constexpr int G = 64 / CF::L, PER = 16 / (int)sizeof(E), CH = 64 * PER;
-  const int lo = (int)threadIdx.x * PER;   // this lane's first element of every chunk
+  wait_lds_reads();
+  const int lo = (int)(threadIdx.x % 64) * PER;   // this lane's first element of every chunk
 #pragma unroll
   for (int gi = 0; gi < G; ++gi) {
     const E* s = src(gi) + lo;
@@ -77,29 +85,45 @@ __device__ __forceinline__ void dma_rows(E* dst, int n, F&& src) {
   }
 }
 
+// Wavefronts per workgroup of the row kernels where a launch has few rows (at most
+// kFewRowGroups wavefronts of them): all work on the same rows, wavefront w on coils
+// w, w + NW, ..., and their sums meet in LDS.  Each forms p itself, which costs the
+// fields' reads NW times over.  Four where their tiles fit 64 KiB of LDS, else two.
+template <class CF>
+constexpr int kRowWaves = 4 * ((64 + CF::L - 1) / CF::L * CF::SPAN + (CF::kRowsDma ? 0 : 64 / CF::L * CF::N)) * 8 <= 60 * 1024 ? 4 : 2;
+
+// Where the line lies, solves of 192 x 160 (8 coils), 256 x 256 (12) and 320 x 320 (15)
+// with one / NW wavefronts per row group: 192-256 groups 726 / 528, 1262 / 939 and
+// 1613 / 986 us, 768-853 groups 934 / 793, 1620 / 1506 and 2371 / 2303 us, 1024-1152
+// groups 1088 / 1069, 1817 / 2030 and 2685 / 2854 us.
+constexpr long kFewRowGroups = 3 * 256;
+
+// sum over a lane group of L lanes, in lane order, by every lane's own wavefront
 template <int L>
-__device__ __forceinline__ double group_reduce2(double v, double* red, int lane) {
-  red[threadIdx.x] = v;
-  __syncthreads();
+__device__ __forceinline__ double group_reduce2(double v, double* red, int tid, int lane) {
+  red[tid] = v;
+  wave_sync();
   double s = 0.0;
   if (lane == 0) {
-    for (int i = 0; i < L; ++i) s += red[threadIdx.x + i];
+    for (int i = 0; i < L; ++i) s += red[tid + i];
   }
-  __syncthreads();
+  wave_sync();
   return s;
 }
 
 // ---------------------------------------------------------------- row pass 1
-template <class CF, int MODE, int ST, bool HALF>
-__global__ __launch_bounds__(64) void k_rows_fwd(Grid2dArgs a) {
+template <class CF, int MODE, int ST, bool HALF, int NW>
+__global__ __launch_bounds__(64 * NW) void k_rows_fwd(Grid2dArgs a) {
   constexpr int L = CF::L, G = 64 / L, NG = (64 + L - 1) / L;
   constexpr int VA = CF::VA, VB = CF::VB;
   // HALF (the Toeplitz grids, nx = Gx / 2): values m >= VA / 2 lie past the
   // image row, so they are compile-time zeros in the forward transform
   constexpr int VAH = HALF ? VA / 2 : VA;
-  __shared__ float2 lds_all[NG * CF::SPAN];
+  __shared__ float2 lds_waves[NW * NG * CF::SPAN];
   __shared__ double red[64 + L];   // lane 0 of a partial last group reads L entries
-  const int g = threadIdx.x / L, lane = threadIdx.x % L;
+  const int wave = NW > 1 ? threadIdx.x / 64 : 0, tid = NW > 1 ? threadIdx.x % 64 : threadIdx.x;
+  float2* lds_all = lds_waves + wave * NG * CF::SPAN;
+  const int g = tid / L, lane = tid % L;
   const long gid = (long)blockIdx.x * G + g;
   const bool active = g < G && gid < (long)a.K * a.ny;
   const long gg = active ? gid : 0;
@@ -121,7 +145,7 @@ __global__ __launch_bounds__(64) void k_rows_fwd(Grid2dArgs a) {
       else return (const ME*)(a.maps + moff);
     });
   };
-  if constexpr (DMA) map_rows(0);
+  if constexpr (DMA) if (wave < a.nc) map_rows(wave);
 
   const size_t rowoff = ((size_t)k * a.ny + y) * a.nx;
   // the per-probe fields never alias one another: restrict lets every load of
@@ -138,6 +162,8 @@ __global__ __launch_bounds__(64) void k_rows_fwd(Grid2dArgs a) {
     alpha = (float)a.alpha[k];
     beta = (float)a.beta[k];
   }
+  // every wavefront forms p of the rows from the old fields; once all have read
+  // them, the wavefronts write x, r and p, a share of the elements each
 #pragma unroll
   for (int m = 0; m < VA; ++m) {
     if (HALF && m >= VAH) {   // past the image row
@@ -149,9 +175,9 @@ __global__ __launch_bounds__(64) void k_rows_fwd(Grid2dArgs a) {
     const size_t i = rowoff + (ok ? xx : 0);   // in-bounds address for every lane
     float2 val = make_float2(0.f, 0.f);
     if constexpr (MODE == C1_FIRST_PROBE) {
-      val = draw_probe(arg_seed(a), arg_first(a) + k, (uint32_t)(y * a.nx + xx), 0u, a.dist);
+      val = draw_probe(arg_seed(a), arg_first(a) + a.k0 + k, (uint32_t)(y * a.nx + xx), 0u, a.dist);
       if (!ok) val = make_float2(0.f, 0.f);
-      if (active && ok) { R[i] = val; P[i] = val; }
+      if (active && ok && m % NW == wave) { R[i] = val; P[i] = val; }
       d0 += (double)val.x * val.x + (double)val.y * val.y;
     } else if constexpr (MODE == C1_FIRST_BUF) {
       // loads go out on every lane (the address is in bounds) and lanes
@@ -159,27 +185,35 @@ __global__ __launch_bounds__(64) void k_rows_fwd(Grid2dArgs a) {
       // condition (or as an operand of a select) gets a branch and a wait
       // of its own
       val = cscale(R[i], ok ? 1.f : 0.f);
-      if (active && ok) P[i] = val;
+      if (active && ok && m % NW == wave) P[i] = val;
       d0 += (double)val.x * val.x + (double)val.y * val.y;
     } else if constexpr (MODE == C1_ITER) {
-      val = make_float2(0.f, 0.f);   // the update runs below, all loads first
+      val = make_float2(0.f, 0.f);
+      if constexpr (NW > 1) {   // p of iteration i; the fields are updated below
+        const float2 rn = cfma(R[i], -alpha, Q[i]);
+        val = cfma(rn, beta, P[i]);
+        if (!ok) val = make_float2(0.f, 0.f);
+        else d0 += (double)rn.x * rn.x + (double)rn.y * rn.y;
+      }
     } else {  // C1_APPLY
       val = cscale(SRC[i], ok ? a.scale : 0.f);
     }
     pv[m] = val;
   }
   if constexpr (MODE == C1_ITER) {
-    // finish iteration i-1 and start i: x += alpha p, r -= alpha q, p = r + beta p.
-    // In chunks of H elements, every load of a chunk is issued before its first store.
-    constexpr int H = VAH > 8 ? 8 : VAH;
+    // finish iteration i-1 and start i: x += alpha p, r -= alpha q, p = r + beta p,
+    // a share of the elements for each wavefront.  In chunks of H elements, every
+    // load of a chunk is issued before its first store.
+    constexpr int S = (VAH + NW - 1) / NW, H = S > 8 ? 8 : S;
+    if constexpr (NW > 1) __syncthreads();
     const bool xz = a.x_zero != 0;
 #pragma unroll
-    for (int m0 = 0; m0 < VAH; m0 += H) {
+    for (int m0 = 0; m0 < S; m0 += H) {
       float2 po[H], qo[H], ro[H], xo[H];
 #pragma unroll
       for (int h = 0; h < H; ++h) {
-        if (m0 + h >= VAH) break;
-        const int xx = CF::posA(lane, m0 + h);
+        if (m0 + h >= S) break;
+        const int m = NW > 1 ? min(wave * S + m0 + h, VAH - 1) : m0 + h, xx = CF::posA(lane, m);
         const size_t i = rowoff + ((inA && xx < a.nx) ? xx : 0);
         po[h] = P[i];
         qo[h] = Q[i];
@@ -188,25 +222,29 @@ __global__ __launch_bounds__(64) void k_rows_fwd(Grid2dArgs a) {
       }
 #pragma unroll
       for (int h = 0; h < H; ++h) {
-        const int m = m0 + h;
-        if (m >= VAH) break;
-        const int xx = CF::posA(lane, m);
-        const bool ok = inA && xx < a.nx;
+        if (m0 + h >= S) break;
+        const int m = wave * S + m0 + h, xx = CF::posA(lane, m);
+        const bool ok = inA && m < VAH && xx < a.nx;
         const size_t i = rowoff + (ok ? xx : 0);
         const float2 rn = ok ? cfma(ro[h], -alpha, qo[h]) : make_float2(0.f, 0.f);
-        pv[m] = ok ? cfma(rn, beta, po[h]) : make_float2(0.f, 0.f);
+        const float2 pn = ok ? cfma(rn, beta, po[h]) : make_float2(0.f, 0.f);
         if (active && ok) {
           X[i] = cfma(xz ? make_float2(0.f, 0.f) : xo[h], alpha, po[h]);
           R[i] = rn;
-          P[i] = pv[m];
+          P[i] = pn;
         }
-        d0 += (double)rn.x * rn.x + (double)rn.y * rn.y;
+        if constexpr (NW == 1) {
+          pv[m0 + h] = pn;
+          d0 += (double)rn.x * rn.x + (double)rn.y * rn.y;
+        }
       }
     }
   }
   if constexpr (MODE != C1_APPLY) {
-    d0 = group_reduce2<L>(d0, red, lane);
-    if (active && lane == 0) a.part[((size_t)k * a.ny + y) * 4] = d0;
+    if (wave == 0) {
+      d0 = group_reduce2<L>(d0, red, tid, lane);
+      if (active && lane == 0) a.part[((size_t)k * a.ny + y) * 4] = d0;
+    }
   }
 
   float2* __restrict__ T = a.T;
@@ -228,8 +266,8 @@ __global__ __launch_bounds__(64) void k_rows_fwd(Grid2dArgs a) {
       svn[m] = map_raw<ST>(a, moff + ((inA && xx < a.nx) ? xx : 0));
     }
   };
-  if constexpr (PF) load_maps(0);
-  for (int c = 0; c < a.nc; ++c) {
+  if constexpr (PF) if (wave < a.nc) load_maps(wave);
+  for (int c = wave; c < a.nc; c += NW) {
     float2 v[CF::VMAX];
     if constexpr (PF) {
 #pragma unroll
@@ -240,7 +278,7 @@ __global__ __launch_bounds__(64) void k_rows_fwd(Grid2dArgs a) {
         }
         v[m] = cmul(widen(svn[m]), pv[m]);   // pv is 0 outside the row
       }
-      if (c + 1 < a.nc) load_maps(c + 1);
+      if (c + NW < a.nc) load_maps(c + NW);
     } else if constexpr (DMA) {
       wait_lds_loads();
       const ME* mrow = reinterpret_cast<const ME*>(lds);
@@ -269,7 +307,7 @@ __global__ __launch_bounds__(64) void k_rows_fwd(Grid2dArgs a) {
     }
     CF::template forward<false>(v, lds, lane, tw);
     if constexpr (DMA) {
-      if (c + 1 < a.nc) map_rows(c + 1);
+      if (c + NW < a.nc) map_rows(c + NW);
     }
     if (active && inB) {
       const size_t off = (((size_t)k * a.nc + c) * a.ny + y) * a.Gx;
@@ -368,16 +406,18 @@ __global__ __launch_bounds__(CP::THREADS) void k_cols(Grid2dArgs a) {
 }
 
 // ---------------------------------------------------------------- row pass 2
-template <class CF, int MODE, int ST, bool HALF>
-__global__ __launch_bounds__(64) void k_rows_inv(Grid2dArgs a) {
+template <class CF, int MODE, int ST, bool HALF, int NW>
+__global__ __launch_bounds__(64 * NW) void k_rows_inv(Grid2dArgs a) {
   constexpr int L = CF::L, G = 64 / L, NG = (64 + L - 1) / L;
   constexpr int VA = CF::VA, VB = CF::VB;
   // HALF (the Toeplitz grids, nx = Gx / 2): only values m < VA / 2 of the
   // inverse transform lie in the image row
   constexpr int VAH = HALF ? VA / 2 : VA;
-  __shared__ float2 lds_all[NG * CF::SPAN];
-  __shared__ double red[64 + L];   // lane 0 of a partial last group reads L entries
-  const int g = threadIdx.x / L, lane = threadIdx.x % L;
+  __shared__ float2 lds_waves[NW * NG * CF::SPAN];
+  __shared__ double red[NW * 3 * (64 + L)];   // the sums of a partial last group read past the wavefront
+  const int wave = NW > 1 ? threadIdx.x / 64 : 0, tid = NW > 1 ? threadIdx.x % 64 : threadIdx.x;
+  float2* lds_all = lds_waves + wave * NG * CF::SPAN;
+  const int g = tid / L, lane = tid % L;
   const long gid = (long)blockIdx.x * G + g;
   const bool active = g < G && gid < (long)a.K * a.ny;
   const long gg = active ? gid : 0;
@@ -406,13 +446,14 @@ __global__ __launch_bounds__(64) void k_rows_inv(Grid2dArgs a) {
       else return (const TE*)(T + off);
     });
   };
-  if constexpr (DMA) t_rows(0);
+  if constexpr (DMA) if (wave < a.nc) t_rows(wave);
   // Stockham rows of 512 and 768 points: each coil's map rows come through LDS (a
   // buffer of their own, fetched when the coil starts and read after its
   // inverse transform); with the transformed row of the next coil already in
   // registers, the combine's own loads would be serialised for want of them
   using ME = MapElem<ST>;
-  __shared__ ME mapbuf[PF ? G * CF::N : 1];
+  __shared__ ME mapbufs[PF ? NW * G * CF::N : 1];
+  ME* mapbuf = mapbufs + (PF ? wave * G * CF::N : 0);
   auto map_rows = [&](int c) {
     dma_rows<CF, ME, CF::N>(mapbuf, a.nx, [&](int gi) {
       const long gq = (long)blockIdx.x * G + gi;
@@ -422,28 +463,9 @@ __global__ __launch_bounds__(64) void k_rows_inv(Grid2dArgs a) {
       else return (const ME*)(a.maps + moff);
     });
   };
-  // p (or scale * src) of this row: lam p enters q first (when lam != 0); the
-  // dots at the end load it again
-  auto load_p = [&](float2* pa) {
+  float2 qa[CF::VMAX];   // sum over this wavefront's coils
 #pragma unroll
-    for (int m = 0; m < VA; ++m) {
-      if (HALF && m >= VAH) continue;   // past the image row (zero)
-      const int xx = CF::posA(lane, m);
-      const bool ok = inA && xx < a.nx;
-      const size_t i = rowoff + (ok ? xx : 0);
-      const float2 raw = MODE == C1_APPLY ? SRC[i] : P[i];
-      pa[m] = cscale(raw, ok ? (MODE == C1_APPLY ? a.scale : 1.f) : 0.f);
-    }
-  };
-  float2 qa[CF::VMAX];
-  if (a.lam != 0.f) {
-    load_p(qa);
-#pragma unroll
-    for (int m = 0; m < VAH; ++m) qa[m] = cscale(qa[m], a.lam);
-  } else {
-#pragma unroll
-    for (int m = 0; m < VAH; ++m) qa[m] = make_float2(0.f, 0.f);
-  }
+  for (int m = 0; m < VAH; ++m) qa[m] = make_float2(0.f, 0.f);
   // Stockham rows of 512 and 768 points: the transformed row of coil c + 1 is loaded
   // while coil c is inverted (raw storage form, unconditional loads from
   // in-row addresses; lanes outside layout B get zeros at use)
@@ -457,14 +479,14 @@ __global__ __launch_bounds__(64) void k_rows_inv(Grid2dArgs a) {
       else tn[r] = T[j];
     }
   };
-  if constexpr (PF) load_row(0);
-  for (int c = 0; c < a.nc; ++c) {
+  if constexpr (PF) if (wave < a.nc) load_row(wave);
+  for (int c = wave; c < a.nc; c += NW) {
     float2 v[CF::VMAX];
     if constexpr (PF) {
 #pragma unroll
       for (int r = 0; r < VB; ++r) v[r] = widen(tn[r]);   // unused outside layout B
       map_rows(c);
-      if (c + 1 < a.nc) load_row(c + 1);
+      if (c + NW < a.nc) load_row(c + NW);
     } else if constexpr (DMA) {
       wait_lds_loads();
       const TE* trow = reinterpret_cast<const TE*>(lds);
@@ -482,7 +504,7 @@ __global__ __launch_bounds__(64) void k_rows_inv(Grid2dArgs a) {
     }
     CF::template inverse<true>(v, lds, lane, tw);
     if constexpr (DMA) {
-      if (c + 1 < a.nc) t_rows(c + 1);
+      if (c + NW < a.nc) t_rows(c + NW);
     }
     // the combine is unconditional (lanes outside the row are never stored
     // or summed)
@@ -507,38 +529,47 @@ __global__ __launch_bounds__(64) void k_rows_inv(Grid2dArgs a) {
       }
     }
   }
-  float2 pa[CF::VMAX], ra[CF::VMAX];
-  load_p(pa);
+  // the wavefronts' sums meet in their tiles; each takes a share of the elements
+  // (added in wavefront order), with lam p, q's store and the dots
+  static_assert(NW == 1 || VAH * 64 <= NG * CF::SPAN, "a wavefront's sums fit its tile");
+  constexpr int H = (VAH + NW - 1) / NW;
+  if constexpr (NW > 1) {
 #pragma unroll
-  for (int m = 0; m < VA; ++m) {
-    if (HALF && m >= VAH) continue;   // past the image row (zero)
-    const int xx = CF::posA(lane, m);
-    const size_t i = rowoff + ((inA && xx < a.nx) ? xx : 0);
-    ra[m] = MODE == C1_ITER ? R[i] : pa[m];
+    for (int m = 0; m < VAH; ++m) lds_all[m * 64 + tid] = qa[m];
   }
-  double d1 = 0.0, d2 = 0.0, d3 = 0.0;
+  float2 pa[H], ra[H];   // p (or scale * src) and r of the share
 #pragma unroll
-  for (int m = 0; m < VA; ++m) {
-    if (HALF && m >= VAH) continue;   // past the image row (zero)
-    const int xx = CF::posA(lane, m);
+  for (int h = 0; h < H; ++h) {
+    const int m = min(wave * H + h, VAH - 1), xx = CF::posA(lane, m);
     const bool ok = inA && xx < a.nx;
     const size_t i = rowoff + (ok ? xx : 0);
-    const float2 rv = ra[m];
-    if (ok) {
-      if (active) Qo[i] = qa[m];
-      d1 += (double)pa[m].x * qa[m].x + (double)pa[m].y * qa[m].y;
-      d2 += (double)qa[m].x * qa[m].x + (double)qa[m].y * qa[m].y;
-      d3 += (double)rv.x * qa[m].x + (double)rv.y * qa[m].y;
-    }
+    const float2 raw = MODE == C1_APPLY ? SRC[i] : P[i];
+    pa[h] = cscale(raw, ok ? (MODE == C1_APPLY ? a.scale : 1.f) : 0.f);
+    ra[h] = MODE == C1_ITER ? R[i] : pa[h];
   }
-  d1 = group_reduce2<L>(d1, red, lane);
-  d2 = group_reduce2<L>(d2, red, lane);
-  d3 = group_reduce2<L>(d3, red, lane);
-  if (active && lane == 0) {
-    double* pp = a.part + ((size_t)k * a.ny + y) * 4;
-    pp[1] = d1;
-    pp[2] = d2;
-    pp[3] = d3;
+  if constexpr (NW > 1) __syncthreads();
+  double d[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+  for (int h = 0; h < H; ++h) {
+    const int m = wave * H + h, xx = CF::posA(lane, m);
+    if (m >= VAH || !inA || xx >= a.nx) continue;
+    float2 q = a.lam != 0.f ? cscale(pa[h], a.lam) : make_float2(0.f, 0.f);
+#pragma unroll
+    for (int w = 0; w < NW; ++w) q = cadd(q, NW > 1 ? lds_waves[w * NG * CF::SPAN + m * 64 + tid] : qa[m % VAH]);
+    if (active) Qo[rowoff + xx] = q;
+    d[0] += (double)pa[h].x * q.x + (double)pa[h].y * q.y;
+    d[1] += (double)q.x * q.x + (double)q.y * q.y;
+    d[2] += (double)ra[h].x * q.x + (double)ra[h].y * q.y;
+  }
+#pragma unroll
+  for (int j = 0; j < 3; ++j) red[(wave * 3 + j) * (64 + L) + tid] = d[j];
+  __syncthreads();
+  static_assert(L >= 3, "one lane per sum");
+  if (wave == 0 && active && lane < 3) {   // the three sums of the row, wavefronts and lanes in order
+    double t = 0.0;
+    for (int w = 0; w < NW; ++w)
+      for (int i = 0; i < L; ++i) t += red[(w * 3 + lane) * (64 + L) + tid - lane + i];
+    a.part[((size_t)k * a.ny + y) * 4 + 1 + lane] = t;
   }
 }
 
@@ -590,31 +621,31 @@ static hipError_t with_line(int n, F&& f) {
   }
 }
 
-template <class CF, int ST, bool HALF>
+template <class CF, int ST, bool HALF, int NW>
 static hipError_t rows_fwd_h(int mode, const Grid2dArgs& a, hipStream_t s) {
   constexpr int G = 64 / CF::L;
   const long rows = (long)a.K * a.ny;
-  dim3 grid((unsigned)((rows + G - 1) / G)), block(64);
+  dim3 grid((unsigned)((rows + G - 1) / G)), block(64 * NW);
   switch (mode) {
-    case C1_FIRST_PROBE: hipLaunchKernelGGL((k_rows_fwd<CF, C1_FIRST_PROBE, ST, HALF>), grid, block, 0, s, a); break;
-    case C1_FIRST_BUF: hipLaunchKernelGGL((k_rows_fwd<CF, C1_FIRST_BUF, ST, HALF>), grid, block, 0, s, a); break;
-    case C1_ITER: hipLaunchKernelGGL((k_rows_fwd<CF, C1_ITER, ST, HALF>), grid, block, 0, s, a); break;
-    case C1_APPLY: hipLaunchKernelGGL((k_rows_fwd<CF, C1_APPLY, ST, HALF>), grid, block, 0, s, a); break;
+    case C1_FIRST_PROBE: hipLaunchKernelGGL((k_rows_fwd<CF, C1_FIRST_PROBE, ST, HALF, NW>), grid, block, 0, s, a); break;
+    case C1_FIRST_BUF: hipLaunchKernelGGL((k_rows_fwd<CF, C1_FIRST_BUF, ST, HALF, NW>), grid, block, 0, s, a); break;
+    case C1_ITER: hipLaunchKernelGGL((k_rows_fwd<CF, C1_ITER, ST, HALF, NW>), grid, block, 0, s, a); break;
+    case C1_APPLY: hipLaunchKernelGGL((k_rows_fwd<CF, C1_APPLY, ST, HALF, NW>), grid, block, 0, s, a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
-template <class CF, int ST, bool HALF>
+template <class CF, int ST, bool HALF, int NW>
 static hipError_t rows_inv_h(int mode, const Grid2dArgs& a, hipStream_t s) {
   constexpr int G = 64 / CF::L;
   const long rows = (long)a.K * a.ny;
-  dim3 grid((unsigned)((rows + G - 1) / G)), block(64);
+  dim3 grid((unsigned)((rows + G - 1) / G)), block(64 * NW);
   switch (mode) {
     case C1_FIRST_PROBE: case C1_FIRST_BUF:
-      hipLaunchKernelGGL((k_rows_inv<CF, C1_FIRST_BUF, ST, HALF>), grid, block, 0, s, a); break;
-    case C1_ITER: hipLaunchKernelGGL((k_rows_inv<CF, C1_ITER, ST, HALF>), grid, block, 0, s, a); break;
-    case C1_APPLY: hipLaunchKernelGGL((k_rows_inv<CF, C1_APPLY, ST, HALF>), grid, block, 0, s, a); break;
+      hipLaunchKernelGGL((k_rows_inv<CF, C1_FIRST_BUF, ST, HALF, NW>), grid, block, 0, s, a); break;
+    case C1_ITER: hipLaunchKernelGGL((k_rows_inv<CF, C1_ITER, ST, HALF, NW>), grid, block, 0, s, a); break;
+    case C1_APPLY: hipLaunchKernelGGL((k_rows_inv<CF, C1_APPLY, ST, HALF, NW>), grid, block, 0, s, a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -624,18 +655,24 @@ static hipError_t rows_inv_h(int mode, const Grid2dArgs& a, hipStream_t s) {
 // (the Toeplitz grids, nx = Gx / 2)
 template <class CF, int ST>
 static hipError_t rows_fwd(int mode, const Grid2dArgs& a, hipStream_t s) {
+  constexpr int G = 64 / CF::L;
+  const bool few = ((long)a.K * a.ny + G - 1) / G <= kFewRowGroups;
   if constexpr (CF::VA % 2 == 0) {
-    if (2 * a.nx == a.Gx) return rows_fwd_h<CF, ST, true>(mode, a, s);
+    if (2 * a.nx == a.Gx)
+      return few ? rows_fwd_h<CF, ST, true, kRowWaves<CF>>(mode, a, s) : rows_fwd_h<CF, ST, true, 1>(mode, a, s);
   }
-  return rows_fwd_h<CF, ST, false>(mode, a, s);
+  return few ? rows_fwd_h<CF, ST, false, kRowWaves<CF>>(mode, a, s) : rows_fwd_h<CF, ST, false, 1>(mode, a, s);
 }
 
 template <class CF, int ST>
 static hipError_t rows_inv(int mode, const Grid2dArgs& a, hipStream_t s) {
+  constexpr int G = 64 / CF::L;
+  const bool few = ((long)a.K * a.ny + G - 1) / G <= kFewRowGroups;
   if constexpr (CF::VA % 2 == 0) {
-    if (2 * a.nx == a.Gx) return rows_inv_h<CF, ST, true>(mode, a, s);
+    if (2 * a.nx == a.Gx)
+      return few ? rows_inv_h<CF, ST, true, kRowWaves<CF>>(mode, a, s) : rows_inv_h<CF, ST, true, 1>(mode, a, s);
   }
-  return rows_inv_h<CF, ST, false>(mode, a, s);
+  return few ? rows_inv_h<CF, ST, false, kRowWaves<CF>>(mode, a, s) : rows_inv_h<CF, ST, false, 1>(mode, a, s);
 }
 
 template <class CP, bool TB, bool PAD>
@@ -651,7 +688,7 @@ static hipError_t cols(const Grid2dArgs& a, hipStream_t s) {
 // One application of the normal operator (three passes) with storage ST:
 // 0 complex64, 1 bfloat16 maps, 2 bfloat16 maps and planes
 template <int ST>
-static hipError_t grid_normal(int mode, const Grid2dArgs& a, hipStream_t s) {
+static hipError_t grid_passes(int mode, const Grid2dArgs& a, hipStream_t s) {
   hipError_t e = with_line(a.Gx, [&](auto cf) { return rows_fwd<decltype(cf), ST>(mode, a, s); });
   if (e != hipSuccess) return e;
   e = with_col(a.ny, [&](auto cp) {
@@ -667,6 +704,57 @@ static hipError_t grid_normal(int mode, const Grid2dArgs& a, hipStream_t s) {
   });
   if (e != hipSuccess) return e;
   return with_line(a.Gx, [&](auto cf) { return rows_inv<decltype(cf), ST>(mode, a, s); });
+}
+
+// Probes per pass.  The planes cross memory four times an iteration (written, column
+// pass in place, read); a set of probes whose planes fit the last-level cache (256 MiB,
+// less the fields that pass through) goes through all three passes while they are
+// there, and every set reuses the same stretch of T.  Where the rows of such a set fill
+// the wavefront slots of the row kernels (two per SIMD, 256 CUs) more than once, the set is cut
+// to whole rounds, unless that leaves less than 96 MiB and the gaps between the shorter
+// launches show.  Solves, one pass / sets of about 208 MiB: 256 x 256 spiral (16 coils, K = 64)
+// 18.3 / 15.9 ms, 128 x 128 spiral (20 coils, K = 128) 11.2 / 9.3, 256 x 256 masked (12 coils,
+// K = 128) 13.7 / 11.2, 288 x 288 masked (20, K = 64) 15.8 / 14.5; 1706 wavefronts / 3413:
+// 160 x 160 spiral (8 coils) 7.2 / 7.5 ms, 320 x 320 masked (8) 13.3 / 13.9; sets of
+// 64 MiB are slower than one pass (20.8, 11.6, 17.2, 17.0 ms).
+inline int grid_chunk(int K, int ny, int group, size_t plane) {
+  const size_t most = 216u << 20, least = 96u << 20;
+  if (K * plane <= most) return K;
+  const size_t fit = std::max<size_t>(1, most / plane);
+  const size_t round = (size_t)group * 256 * 8 / ny;   // probes whose rows fill the slots once
+  size_t set = fit;
+  for (size_t j = 1; round && j * round < fit; ++j)
+    if (j * round * plane >= least) {
+      set = j * round;
+      break;
+    }
+  const size_t n = (K + set - 1) / set;
+  return (int)((K + n - 1) / n);
+}
+
+template <int ST>
+static hipError_t grid_normal(int mode, const Grid2dArgs& all, hipStream_t s) {
+  const size_t plane = (size_t)all.nc * all.ny * all.Gx * (ST == 2 ? 4 : 8), n = (size_t)all.ny * all.nx;
+  int chunk = 0;
+  const hipError_t known = with_line(all.Gx, [&](auto cf) {
+    chunk = grid_chunk(all.K, all.ny, 64 / decltype(cf)::L, plane);
+    return hipSuccess;
+  });
+  if (known != hipSuccess) return known;
+  for (int k0 = 0; k0 < all.K; k0 += chunk) {
+    Grid2dArgs a = all;
+    a.k0 = k0;
+    a.K = std::min(chunk, all.K - k0);
+    for (float2** f : {&a.x, &a.r, &a.p, &a.q})
+      if (*f) *f += k0 * n;
+    if (a.src) a.src += k0 * n;
+    if (a.alpha) a.alpha += k0;
+    if (a.beta) a.beta += k0;
+    if (a.part) a.part += (size_t)k0 * a.ny * 4;
+    const hipError_t e = grid_passes<ST>(mode, a, s);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 }  // namespace pico

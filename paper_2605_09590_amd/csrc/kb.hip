@@ -231,13 +231,6 @@ enum KbSrc : int { KB_READ = 0, KB_NOISE = 1 };
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
-// LDS traffic between the lanes of one wavefront: the hardware keeps a wave's LDS
-// operations in order, this keeps the compiler from moving them
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
-
 // Planes of a data pass: plane p of the launch is image p / cg, coil c0 + p mod cg
 struct KbPlanes {
   int planes, cg, c0, nc;

@@ -119,6 +119,7 @@ struct Grid2dArgs {
   uint64_t seed, first;
   const uint64_t* tp;          // non-NULL: (seed, first) read from device memory here
   int dist;
+  int k0;                      // probes of the call before this launch's first
 };
 
 bool cart1d_supported(int ny);
