@@ -190,42 +190,6 @@ hipError_t launch_extract_rows(const float2* x, double* var, int K, int y0, int 
   return hipGetLastError();
 }
 
-// ------------------------------------------------------------ accumulation
-// PICO: sum += Re(conj v x), sum_im += Im(conj v x), sumsq += Re(.)^2 over the
-// K probes of the tile, in probe order (App. A, Algorithm 1).  PMR: sum +=
-// x, sumsq += |x|^2.
-__global__ void k_accum_colmajor(AccumArgs a) {
-  const int y = blockIdx.x * blockDim.x + threadIdx.x;
-  const int col = blockIdx.y;
-  if (y >= a.ny) return;
-  const uint32_t vox = (uint32_t)(y * a.nx + col);
-  double s = 0.0, si = 0.0, ss = 0.0;
-  for (int k = 0; k < a.K; ++k) {
-    const float2 u = a.x[((size_t)k * a.nx + col) * a.ny + y];
-    if (a.pmr) {
-      s += (double)u.x;
-      si += (double)u.y;
-      ss += (double)u.x * u.x + (double)u.y * u.y;
-    } else {
-      const float2 v = draw_probe(arg_seed(a), arg_first(a) + k, vox, 0u, a.dist);
-      const double re = (double)v.x * u.x + (double)v.y * u.y;
-      const double im = (double)v.x * u.y - (double)v.y * u.x;
-      s += re;
-      si += im;
-      ss += re * re;
-    }
-  }
-  a.sum[vox] += s;
-  if (a.sum_im) a.sum_im[vox] += si;
-  if (a.sumsq) a.sumsq[vox] += ss;
-}
-
-hipError_t launch_accum_colmajor(const AccumArgs& a, hipStream_t s) {
-  dim3 grid((a.ny + 63) / 64, a.nx), block(64);
-  hipLaunchKernelGGL(k_accum_colmajor, grid, block, 0, s, a);
-  return hipGetLastError();
-}
-
 // ------------------------------------------------------------ layout changes
 // v [K][ny][nx] (row-major images) -> out [K][nx][ny]
 __global__ void k_transpose_in(const float2* __restrict__ v, float2* __restrict__ out, int ny, int nx) {

@@ -42,9 +42,12 @@ template <class CP> constexpr int kFoldProbes = 64 / CP::LA;
 
 // Map column of N values into an LDS buffer, straight from global memory (16
 // bytes per lane and instruction, no registers held; N even, so whole pairs);
-// drain_lds_loads() and a barrier come before the first read
+// drain_lds_loads() and a barrier come before the first read, and the reads of what
+// the column overwrites have returned (lgkmcnt 0) before it is asked for: the loads
+// write LDS outside the wavefront's in-order LDS queue
 template <int N>
 __device__ __forceinline__ void stage_column(const float2* src, float2* dst) {
+  __builtin_amdgcn_s_waitcnt(0xC07F);
   const int lo = 2 * (int)threadIdx.x;
 #pragma unroll
   for (int j = 0; j < N; j += 128)

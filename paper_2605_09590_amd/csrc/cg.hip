@@ -3,6 +3,8 @@
 // Vector updates run in float32; inner products are accumulated in float64
 // from exact float32 products and reduced in a fixed order, and every step
 // scalar (alpha, beta, |r|^2) is float64 and stays on the device.
+#include <algorithm>
+
 #include "device_common.h"
 #include "runtime.h"
 
@@ -96,6 +98,66 @@ hipError_t launch_scalars(const ScalarArgs& a, hipStream_t s) {
   hipLaunchKernelGGL(k_scalars, dim3(a.K), dim3(64), 0, s, a);
   return hipGetLastError();
 }
+
+// App. A, Algorithm 1: sum += Re(conj v x), sum_im += Im(conj v x), sumsq += Re(.)^2 over
+// the K probes of the tile (pmr: sum, sum_im += x, sumsq += |x|^2); 64 pixels a
+// workgroup in the fields' order (COL: columns contiguous), the probes in as many
+// contiguous slices as it has wavefronts, joined in slice order.  Bound by the probe
+// draws (Philox and the phase) where the chip is full; one wavefront per 64 pixels
+// filled a fifth of it at 320 x 320 and 64 of its 1024 SIMDs at 64 x 64: 218 -> 123 us
+// (K = 256), 119 -> 43 us (256 x 256, K = 128), 14.2 -> 5.2 us (64 x 64, K = 16).
+constexpr int kAccumSlices = 16;   // at most
+
+template <bool COL>
+__global__ __launch_bounds__(64 * kAccumSlices) void k_accum(AccumArgs a) {
+  __shared__ double part[kAccumSlices][3][64];
+  const int lane = threadIdx.x % 64, w = threadIdx.x / 64, W = blockDim.x / 64;
+  const int n = a.ny * a.nx, i = blockIdx.x * 64 + lane;
+  const bool ok = i < n;
+  const uint32_t vox = COL ? (uint32_t)(i % a.ny * a.nx + i / a.ny) : (uint32_t)i;
+  const int k0 = (int)((long)a.K * w / W), k1 = (int)((long)a.K * (w + 1) / W);
+  double s = 0.0, si = 0.0, ss = 0.0;
+#pragma unroll 2
+  for (int k = k0; k < k1; ++k) {
+    const float2 u = a.x[(size_t)k * n + (ok ? i : 0)];
+    if (a.pmr) {
+      s += (double)u.x;
+      si += (double)u.y;
+      ss += (double)u.x * u.x + (double)u.y * u.y;
+    } else {
+      const float2 v = draw_probe(arg_seed(a), arg_first(a) + k, vox, 0u, a.dist);
+      const double re = (double)v.x * u.x + (double)v.y * u.y;
+      const double im = (double)v.x * u.y - (double)v.y * u.x;
+      s += re;
+      si += im;
+      ss += re * re;
+    }
+  }
+  part[w][0][lane] = s;
+  part[w][1][lane] = si;
+  part[w][2][lane] = ss;
+  __syncthreads();
+  if (w != 0 || !ok) return;
+  for (int j = 1; j < W; ++j) {
+    s += part[j][0][lane];
+    si += part[j][1][lane];
+    ss += part[j][2][lane];
+  }
+  a.sum[vox] += s;
+  if (a.sum_im) a.sum_im[vox] += si;
+  if (a.sumsq) a.sumsq[vox] += ss;
+}
+
+// sixteen slices while the pixels alone give less than two wavefronts a SIMD, else four
+template <bool COL>
+static hipError_t accum(const AccumArgs& a, hipStream_t s) {
+  const int groups = (a.ny * a.nx + 63) / 64;
+  const int slices = std::max(1, std::min(a.K, groups < 512 ? kAccumSlices : 4));
+  hipLaunchKernelGGL(k_accum<COL>, dim3(groups), dim3(64 * slices), 0, s, a);
+  return hipGetLastError();
+}
+hipError_t launch_accum_colmajor(const AccumArgs& a, hipStream_t s) { return accum<true>(a, s); }
+hipError_t launch_accum_rowmajor(const AccumArgs& a, hipStream_t s) { return accum<false>(a, s); }
 
 // Convergence monitor: partial sums of (s - s_ref)^2 and s_ref^2 over
 // standard-deviation maps s = sqrt(max(sum / N, 0)), s_ref = sqrt(max(ref, 0));

@@ -305,38 +305,6 @@ hipError_t launch_coil_combine(const float2* T, const float2* maps, float2* out,
   return hipGetLastError();
 }
 
-// ---------------------------------------------------------------- row-major accumulation
-__global__ void k_accum_rowmajor(AccumArgs a) {
-  const int n = a.ny * a.nx;
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  double s = 0.0, si = 0.0, ss = 0.0;
-  for (int k = 0; k < a.K; ++k) {
-    const float2 u = a.x[(size_t)k * n + i];
-    if (a.pmr) {
-      s += (double)u.x;
-      si += (double)u.y;
-      ss += (double)u.x * u.x + (double)u.y * u.y;
-    } else {
-      const float2 v = draw_probe(arg_seed(a), arg_first(a) + k, (uint32_t)i, 0u, a.dist);
-      const double re = (double)v.x * u.x + (double)v.y * u.y;
-      const double im = (double)v.x * u.y - (double)v.y * u.x;
-      s += re;
-      si += im;
-      ss += re * re;
-    }
-  }
-  a.sum[i] += s;
-  if (a.sum_im) a.sum_im[i] += si;
-  if (a.sumsq) a.sumsq[i] += ss;
-}
-
-hipError_t launch_accum_rowmajor(const AccumArgs& a, hipStream_t s) {
-  const int n = a.ny * a.nx;
-  hipLaunchKernelGGL(k_accum_rowmajor, dim3((n + 255) / 256), dim3(256), 0, s, a);
-  return hipGetLastError();
-}
-
 // ---------------------------------------------------------------- map preparation
 // out[c][y][x] = sg(y, x) sum_d Linv[c][d] maps[d][y][x]; sg = (-1)^(y+x) when fold.
 __global__ void k_prep_maps_rowmajor(const float2* __restrict__ maps, const double* __restrict__ linv,
