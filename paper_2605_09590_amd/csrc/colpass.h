@@ -28,10 +28,11 @@ struct ColPlan {
   static constexpr int L = LA > VA ? LA : VA;
   static constexpr int ST = kStrip * (int)sizeof(float2) / (int)sizeof(C);
   static constexpr int THREADS = ST * L;
-  // exchange: Y[a][k] of column j at k KS + ST a + j; an odd multiple of 128
-  // bytes between consecutive k puts the tasks of a wavefront on alternating
-  // halves of the LDS banks
-  static constexpr int KS = ST * (LA % 2 == 0 ? LA + 1 : LA);
+  // exchange: Y[a][k] of column j at k KS + ST (a ^ (k mod 2)) + j, 128 bytes per
+  // task: consecutive tasks of a wavefront are on alternating halves of the LDS
+  // banks in both layouts, with no padding (LA even: the swap stays inside LA)
+  static_assert(LA % 2 == 0, "pairs of tasks swap");
+  static constexpr int KS = ST * LA;
   static constexpr size_t LDS = (size_t)VA * KS * sizeof(C);
   using Fp64 = ColPlan<LA, VA, double2>;
 };
@@ -56,7 +57,7 @@ __device__ __forceinline__ void col_a_out(const C (&x)[CP::VA], const C (&tw)[CP
 #pragma unroll
   for (int k = 0; k < CP::VA; ++k) {
     const C w = INV ? cmake(tw[k].x, -tw[k].y) : tw[k];
-    ex[k * CP::KS + CP::ST * a] = (ODD || k) ? cmul(v[k], w) : v[k];
+    ex[k * CP::KS + CP::ST * (a ^ (k & 1))] = (ODD || k) ? cmul(v[k], w) : v[k];
   }
 }
 
@@ -66,7 +67,7 @@ __device__ __forceinline__ void col_a_in(C (&x)[CP::VA], const C (&tw)[CP::VA], 
   C v[CP::VA];
 #pragma unroll
   for (int k = 0; k < CP::VA; ++k) {
-    const C z = ex[k * CP::KS + CP::ST * a];
+    const C z = ex[k * CP::KS + CP::ST * (a ^ (k & 1))];
     const C w = INV ? cmake(tw[k].x, -tw[k].y) : tw[k];
     v[k] = (ODD || k) ? cmul(z, w) : z;
   }
@@ -80,12 +81,12 @@ __device__ __forceinline__ void col_a_in(C (&x)[CP::VA], const C (&tw)[CP::VA], 
 template <class CP, class C>
 __device__ __forceinline__ void col_b_load(C (&v)[CP::LA], const C* ex, int k) {
 #pragma unroll
-  for (int a = 0; a < CP::LA; ++a) v[a] = ex[k * CP::KS + CP::ST * a];
+  for (int a = 0; a < CP::LA; ++a) v[a] = ex[k * CP::KS + CP::ST * (a ^ (k & 1))];
 }
 template <class CP, class C>
 __device__ __forceinline__ void col_b_store(const C (&v)[CP::LA], C* ex, int k) {
 #pragma unroll
-  for (int a = 0; a < CP::LA; ++a) ex[k * CP::KS + CP::ST * a] = v[a];
+  for (int a = 0; a < CP::LA; ++a) ex[k * CP::KS + CP::ST * (a ^ (k & 1))] = v[a];
 }
 
 // Strip of workgroup b: workgroups go to the eight XCDs in turn, and workgroup

@@ -323,6 +323,18 @@ __global__ __launch_bounds__(64 * NW) void k_rows_fwd(Grid2dArgs a) {
 }
 
 // ---------------------------------------------------------------- column pass
+// Unpadded 320-point columns are held to 128 registers (8 values spilled): three
+// workgroups of five wavefronts share a CU instead of two (solves of 96 probes, 16
+// coils: complex64 23.3 -> 23.1 ms, bfloat16 planes 19.7 -> 17.5 ms).  Padded ones
+// need 200 and spill 32 at 168: left alone (20.9 ms against 28.8).
+template <class CP, bool PAD>
+constexpr int kColWaves = CP::N == 320 && !PAD ? 4 : 1;
+// Padded 288-point columns run 24 x 12 points (six wavefronts and fewer registers in
+// place of five with 190: 18.0 -> 17.2 ms, 12 coils, 48 probes); 32 x 10 and 32 x 12
+// were slower at 320 and 384 points (20.9 / 22.3, 13.8 / 14.2 ms).
+template <class CP>
+using PadPlan = std::conditional_t<CP::N == 288, ColPlan<24, 12>, CP>;
+
 // Per column of a (k, c) plane: transform along y, weights, inverse transform,
 // in place.  PAD (the Toeplitz grids, Gy = 2 ny): the column is the first half
 // of a line of 2 ny points, zero past it, and only the first half of the
@@ -335,7 +347,7 @@ __global__ __launch_bounds__(64 * NW) void k_rows_fwd(Grid2dArgs a) {
 // against 4.4 TB/s for a plain in-place pass over buffers of that size; the
 // staged 512-point transforms this replaces took 1.26 ms with the VALU 93 % busy.
 template <class CP, bool TB, bool PAD>
-__global__ __launch_bounds__(CP::THREADS) void k_cols(Grid2dArgs a) {
+__global__ __launch_bounds__(CP::THREADS, (kColWaves<CP, PAD>)) void k_cols(Grid2dArgs a) {
   constexpr int LA = CP::LA, VA = CP::VA, N = CP::N;
   extern __shared__ float2 dyn[];
   using E = std::conditional_t<TB, uint32_t, float2>;
@@ -695,7 +707,7 @@ static hipError_t grid_passes(int mode, const Grid2dArgs& a, hipStream_t s) {
     using CP = decltype(cp);
     // padded lines have 64 to 768 points, unpadded ones (2-D masks) too
     if constexpr (CP::N <= 384) {
-      if (a.Gy == 2 * a.ny) return cols<CP, ST == 2, true>(a, s);
+      if (a.Gy == 2 * a.ny) return cols<PadPlan<CP>, ST == 2, true>(a, s);
     }
     if constexpr (CP::N >= 64 && CP::N != 80 && CP::N != 144) {
       if (a.Gy == a.ny) return cols<CP, ST == 2, false>(a, s);
@@ -709,10 +721,11 @@ static hipError_t grid_passes(int mode, const Grid2dArgs& a, hipStream_t s) {
 // Probes per pass.  The planes cross memory four times an iteration (written, column
 // pass in place, read); a set of probes whose planes fit the last-level cache (256 MiB,
 // less the fields that pass through) goes through all three passes while they are
-// there, and every set reuses the same stretch of T.  Where the rows of such a set fill
-// the wavefront slots of the row kernels (two per SIMD, 256 CUs) more than once, the set is cut
-// to whole rounds, unless that leaves less than 96 MiB and the gaps between the shorter
-// launches show.  Solves, one pass / sets of about 208 MiB: 256 x 256 spiral (16 coils, K = 64)
+// there, and every set reuses the same stretch of T.  Of the sets of 96 MiB (below,
+// the gaps between the shorter launches show) to 216 MiB that one takes whose row
+// launches need the fewest rounds of the chip in all (2048 wavefronts: two per SIMD,
+// 256 CUs), the smallest on a tie.
+// Solves, one pass / sets of about 208 MiB: 256 x 256 spiral (16 coils, K = 64)
 // 18.3 / 15.9 ms, 128 x 128 spiral (20 coils, K = 128) 11.2 / 9.3, 256 x 256 masked (12 coils,
 // K = 128) 13.7 / 11.2, 288 x 288 masked (20, K = 64) 15.8 / 14.5; 1706 wavefronts / 3413:
 // 160 x 160 spiral (8 coils) 7.2 / 7.5 ms, 320 x 320 masked (8) 13.3 / 13.9; sets of
@@ -721,15 +734,19 @@ inline int grid_chunk(int K, int ny, int group, size_t plane) {
   const size_t most = 216u << 20, least = 96u << 20;
   if (K * plane <= most) return K;
   const size_t fit = std::max<size_t>(1, most / plane);
-  const size_t round = (size_t)group * 256 * 8 / ny;   // probes whose rows fill the slots once
-  size_t set = fit;
-  for (size_t j = 1; round && j * round < fit; ++j)
-    if (j * round * plane >= least) {
-      set = j * round;
-      break;
+  long best = -1;
+  int set = (int)fit;
+  for (long n = (K + fit - 1) / fit; n <= K; ++n) {
+    const long c = (K + n - 1) / n, full = K / c, rest = K - full * c;
+    if (best >= 0 && c * plane < least) break;
+    const auto rounds = [&](long k) { return (k * ny + group * 2048L - 1) / (group * 2048L); };
+    const long all = full * rounds(c) + rounds(rest);
+    if (best < 0 || all <= best) {
+      best = all;
+      set = (int)c;
     }
-  const size_t n = (K + set - 1) / set;
-  return (int)((K + n - 1) / n);
+  }
+  return set;
 }
 
 template <int ST>

@@ -52,7 +52,9 @@ def _operator(lib, kind, ny, nx, nc, tile):
     ("cart2d", 64, 768, 3, 2, (0, 1)),              # two wavefronts
     ("spiral", 64, 256, 3, 2, (0, 1)),              # 512 points, half rows
     ("spiral", 80, 32, 7, 3, (0, 2)),
-    ("cart2d", 256, 256, 7, 70, (0, 23, 24, 47, 48, 69)),   # 245 MiB of planes: sets of 24, 24 and 22
+    ("cart2d", 256, 256, 7, 71, (0, 35, 36, 70)),   # 249 MiB of planes: sets of 36 and 35
+    ("spiral", 288, 32, 3, 2, (0, 1)),              # padded columns with a plan of their own
+    ("spiral", 320, 48, 2, 2, (0, 1)),
 ])
 def test_products(kind, ny, nx, nc, K, check):
     from paper_2605_09590_amd import pico as lib
@@ -75,7 +77,7 @@ def test_products(kind, ny, nx, nc, K, check):
 @pytest.mark.parametrize("ny,nx,nc,K", [
     (192, 160, 3, 4),      # several wavefronts on the same rows
     (256, 256, 7, 35),     # one wavefront, one set
-    (256, 256, 7, 70),     # sets: every probe drawn from its own index
+    (256, 256, 7, 71),     # sets: every probe drawn from its own index
 ])
 def test_drawn_probes(ny, nx, nc, K):
     from paper_2605_09590_amd import pico as lib
