@@ -871,10 +871,6 @@ pico_status_t estimate_bytes(const pico_op_desc_t* d, size_t* resident, size_t* 
   if (colmajor) {
     add(ny * 4);
     add(ny * 8);
-    if (!wants_gram(d) && !wants_gram16(d)) {
-      add(n * nc * 8);
-      add(6 * n * 4);
-    }
     if (wants_gram(d)) {
       add(gram_bytes(d->ny, d->nx));
       add(ny * 16);
@@ -1045,17 +1041,23 @@ pico_status_t pico::init_in_arena(const pico_op_desc_t* d, void* stream, pico::D
     if ((e = hipMemcpyAsync(op->twt, tw.data(), ny * sizeof(float2), hipMemcpyHostToDevice, s)) != hipSuccess) return bad(e, "upload");
     if ((e = pico::launch_prep_maps_cart1d((const float2*)d->maps, linv_d, op->maps, nc, ny, nx, s)) != hipSuccess) return bad(e, "prep maps");
     if (op->maps_bf && (e = pico::launch_quantise_maps(op->maps, op->maps_bf, (long)(n * nc), true, s)) != hipSuccess) return bad(e, "bfloat16 maps");
+    if (!wants_gram(d) && !wants_gram16(d)) op->rho = 0;   // unsplit: one class of all frequencies
     if (!wants_gram(d) && !wants_gram16(d)) {
-      // room for any mask: what the split takes follows from the mask, the
-      // byte count from the description alone
+      // the split form's buffers are beyond the described bytes: with no room for
+      // them (they are not counted) the operator runs unsplit
       float* fg = nullptr;
-      if ((e = op->alloc(&op->fmaps, n * nc)) != hipSuccess) return bad(e, "class maps");
-      if ((e = op->alloc(&fg, 6 * n)) != hipSuccess) return bad(e, "class blocks");
+      const size_t held = op->bytes, top = op->peak;
+      const bool room = op->alloc(&op->fmaps, n * nc) == hipSuccess && op->alloc(&fg, 6 * n) == hipSuccess;
+      op->bytes = held;
+      op->peak = top;
+      if (!room) (void)hipGetLastError();
+      if (room) {
       const pico::Fold f = pico::fold_of(mask_h.data(), ny);
       op->split = f.split;
       op->rho = f.part.empty() ? -1 : f.part[0];
       if (!f.full.empty()) op->fgram = fg;
       if ((e = pico::build_fold(f, op->maps, nc, ny, nx, op->fmaps, op->fgram, s)) != hipSuccess) return bad(e, "class maps");
+      }
     }
     if (wants_gram(d)) {
       if ((e = op->alloc(&op->gram, pico::gram_bytes(ny, nx) / sizeof(float2))) != hipSuccess) return bad(e, "dense blocks");
