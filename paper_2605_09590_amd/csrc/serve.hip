@@ -146,7 +146,7 @@ struct pico_server_s {
   std::vector<std::unique_ptr<Request>> active;
   std::vector<std::unique_ptr<CachedOp>> cache;   // resident operators, busy or idle
   uint64_t clock = 0;
-  uint64_t* hash_part = nullptr;                  // [kHashBlocks] in the arena
+  uint64_t* hash_part = nullptr;                  // [kHashBlocks], host memory that kernels write (the budget is the operators')
   size_t reserved = 0;   // resident bytes of every cached operator + peaks of operators being built
   bool blocked = false;   // an admission failed on fragmentation: wait for a completion
   std::thread worker;
@@ -280,18 +280,14 @@ struct pico_server_s {
                 {d.mask, d.sampling == PICO_CART_1D ? (uint64_t)d.ny : d.sampling == PICO_CART_2D ? (uint64_t)n : 0},
                 {d.traj, d.sampling == PICO_NONCART ? (uint64_t)d.nsamples * 8 : 0},
                 {d.kdata, d.recon != PICO_CGSENSE ? (uint64_t)d.ncoils * n * 8 : 0}};
-    std::vector<uint64_t> part(kHashBlocks);
     for (const Arr& a : arrs) {
       h = mix_host(h, a.p && a.bytes ? a.bytes : 0);
       if (!a.p || !a.bytes) continue;
       hipLaunchKernelGGL(k_hash_words, dim3(kHashBlocks), dim3(256), 0, st, static_cast<const uint8_t*>(a.p),
                          a.bytes, hash_part);
-      if (hipGetLastError() != hipSuccess ||
-          hipMemcpyAsync(part.data(), hash_part, kHashBlocks * 8, hipMemcpyDeviceToHost, st) != hipSuccess ||
-          hipStreamSynchronize(st) != hipSuccess)
-        return false;
+      if (hipGetLastError() != hipSuccess || hipStreamSynchronize(st) != hipSuccess) return false;
       uint64_t x = 0;
-      for (uint64_t v : part) x ^= v;
+      for (int i = 0; i < kHashBlocks; ++i) x ^= hash_part[i];
       h = mix_host(h, x);
     }
     *out = h;
@@ -461,16 +457,18 @@ pico_status_t pico_server_create(uint64_t hbm_budget, int32_t max_slots, int32_t
     return pico::set_error(e == hipErrorOutOfMemory ? PICO_ENOMEM : PICO_EDEVICE,
                            std::string("server budget: ") + hipGetErrorString(e));
   srv->arena.base = static_cast<char*>(base);
-  srv->hash_part = static_cast<uint64_t*>(srv->arena.alloc(kHashBlocks * sizeof(uint64_t)));
-  if (!srv->hash_part) {
+  void* part = nullptr;
+  if ((e = hipHostMalloc(&part, kHashBlocks * sizeof(uint64_t), hipHostMallocDefault)) != hipSuccess) {
     pico::dev_free(base, srv->base_by);
-    return pico::set_error(PICO_EINVAL, "hbm_budget too small");
+    return pico::set_error(e == hipErrorOutOfMemory ? PICO_ENOMEM : PICO_EDEVICE,
+                           std::string("server: ") + hipGetErrorString(e));
   }
-  srv->reserved = pico::OffsetArena::round_up(kHashBlocks * sizeof(uint64_t));
+  srv->hash_part = static_cast<uint64_t*>(part);
   for (int i = 0; i < max_slots; ++i) {
     hipStream_t s = nullptr;
     if ((e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking)) != hipSuccess) {
       for (hipStream_t t : srv->streams) (void)hipStreamDestroy(t);
+      (void)hipHostFree(srv->hash_part);
       pico::dev_free(base, srv->base_by);
       return pico::set_error(PICO_EDEVICE, std::string("stream: ") + hipGetErrorString(e));
     }
@@ -618,6 +616,7 @@ void pico_server_destroy(pico_server_t srv) {
   srv->cache.clear();
   for (hipEvent_t e : srv->ev_pool) (void)hipEventDestroy(e);
   for (hipStream_t s : srv->streams) (void)hipStreamDestroy(s);
+  (void)hipHostFree(srv->hash_part);
   pico::dev_free(srv->arena.base, srv->base_by);
   delete srv;
 }
