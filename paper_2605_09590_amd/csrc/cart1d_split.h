@@ -42,12 +42,10 @@ template <class CP> constexpr int kFoldProbes = 64 / CP::LA;
 
 // Map column of N values into an LDS buffer, straight from global memory (16
 // bytes per lane and instruction, no registers held; N even, so whole pairs);
-// drain_lds_loads() and a barrier come before the first read, and the reads of what
-// the column overwrites have returned (lgkmcnt 0) before it is asked for: the loads
-// write LDS outside the wavefront's in-order LDS queue
+// wait_lds_loads() and a barrier come before the first read
 template <int N>
 __device__ __forceinline__ void stage_column(const float2* src, float2* dst) {
-  __builtin_amdgcn_s_waitcnt(0xC07F);
+  wait_lds_reads();
   const int lo = 2 * (int)threadIdx.x;
 #pragma unroll
   for (int j = 0; j < N; j += 128)
@@ -55,9 +53,6 @@ __device__ __forceinline__ void stage_column(const float2* src, float2* dst) {
       __builtin_amdgcn_global_load_lds((const void*)(src + j + lo),
                                        (__attribute__((address_space(3))) void*)(dst + j), 16, 0, 0);
 }
-// s_waitcnt vmcnt(0): the direct LDS loads count as vector memory operations, and
-// the compiler does not order LDS reads after them
-__device__ __forceinline__ void drain_lds_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 
 template <class CP, int S, int MODE>
 __global__ __launch_bounds__(64, S * CP::VA <= 20 ? 3 : 2) void k_cart1d_split(Cart1dArgs a) {
@@ -153,7 +148,7 @@ __global__ __launch_bounds__(64, S * CP::VA <= 20 ? 3 : 2) void k_cart1d_split(C
   float2 qa[V];   // coil sum of the transforms, unscaled
 #pragma unroll
   for (int i = 0; i < V; ++i) qa[i] = make_float2(0.f, 0.f);
-  drain_lds_loads();
+  wait_lds_loads();
   __syncthreads();
   int on = 0;   // sampled frequencies of layout B's task
   if (nc > 0) {
@@ -192,7 +187,7 @@ __global__ __launch_bounds__(64, S * CP::VA <= 20 ? 3 : 2) void k_cart1d_split(C
 #pragma unroll
       for (int i = 0; i < LA; ++i) exB[i] = b[i];   // the task's own values
     }
-    drain_lds_loads();
+    wait_lds_loads();
     __syncthreads();
     if (active) {
       float2 z[VA];

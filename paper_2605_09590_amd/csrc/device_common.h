@@ -159,6 +159,21 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_wave_barrier();
 }
 
+// Around direct global -> LDS loads (__builtin_amdgcn_global_load_lds), which write LDS
+// outside the wavefront's in-order LDS queue and which the compiler does not order
+// against LDS accesses:
+// - before the first read of what they bring, s_waitcnt vmcnt(0) (they count as vector
+//   memory operations, and their data is in LDS once the counter has drained; expcnt
+//   and lgkmcnt left at their maxima);
+__device__ __forceinline__ void wait_lds_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }
+// - before they go out, the reads of what they overwrite have returned (lgkmcnt 0), and
+//   the fence and the barrier keep the compiler from moving those reads past this point
+__device__ __forceinline__ void wait_lds_reads() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+  __builtin_amdgcn_s_waitcnt(0xC07F);
+  __builtin_amdgcn_wave_barrier();
+}
+
 // ---------------------------------------------------------------- static_for
 template <int B, int E, typename F>
 __device__ __forceinline__ void static_for(F&& f) {

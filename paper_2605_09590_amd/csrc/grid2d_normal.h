@@ -55,19 +55,6 @@ __device__ __forceinline__ float2 map_at(const Grid2dArgs& a, size_t i) { return
 // idle between two transforms; wait_lds_loads() precedes the first LDS read
 // of the row.  Rows are 16-byte aligned (n and the row pitch multiples of
 // 16 / E).
-// s_waitcnt vmcnt(0) (expcnt and lgkmcnt left at their maxima): the direct
-// LDS loads count as vector memory operations, and their data is in LDS once
-// the counter has drained.  Issued explicitly before the first read of a
-// fetched row: the compiler does not order LDS reads after these loads.
-__device__ __forceinline__ void wait_lds_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }
-// The loads write LDS outside the wavefront's in-order LDS queue: the reads of what
-// they overwrite have to have returned (lgkmcnt 0) before they go out
-__device__ __forceinline__ void wait_lds_reads() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
-  __builtin_amdgcn_s_waitcnt(0xC07F);
-  __builtin_amdgcn_wave_barrier();
-}
-
 template <class CF, class E, int GS, class F>
 __device__ __forceinline__ void dma_rows(E* dst, int n, F&& src) {
   constexpr int G = 64 / CF::L, PER = 16 / (int)sizeof(E), CH = 64 * PER;
