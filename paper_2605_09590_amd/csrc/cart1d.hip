@@ -3,6 +3,8 @@
 // and cart1d_split.h) and the CG building blocks of the column-major layout.
 #include "cart1d_normal.h"
 
+#include <cmath>
+
 namespace pico {
 
 bool cart1d_supported(int ny) {
@@ -26,13 +28,14 @@ hipError_t launch_cart1d(int mode, const Cart1dArgs& a, hipStream_t s) {
 
 // ------------------------------------------------------------ split factor
 // The split with the least transform work, at most one partly sampled class
-// (each needs its own copy of the maps): none where every class is full or empty,
+// (whose phase the maps carry): none where every class is full or empty,
 // else one class of ny / S frequencies.  Measured per noise map (12 coils, 128
-// columns, K = 96, CG 6, ms): R = 2 + 24 calibration lines, S = 2, against
-// unsplit 1.50 -> 1.11 (320 points), 1.29 -> 0.94 (256), 2.12 -> 1.54 (384),
-// 0.69 -> 0.59 (128), 0.41 -> 0.41 (64); uniform R = 2 1.50 -> 0.65 (320), 0.41
-// -> 0.22 (64).  R = 3 with calibration lines leaves two classes of S = 3, which
-// ran slower than unsplit (192 points 0.88 -> 1.17, 288 1.51 -> 1.54).
+// columns, K = 96, CG 20, ms): R = 2 + 24 calibration lines, S = 2, against
+// unsplit 2.37 -> 1.79 (320 points), 2.02 -> 1.50 (256), 3.36 -> 2.36 (384),
+// 1.12 -> 0.90 (128), 0.65 -> 0.57 (64); uniform R = 2 2.46 -> 1.06 (320), 0.64
+// -> 0.29 (64).  Few probes gain least: 320 points, K = 32 1.19 -> 1.03, K = 12 0.88 ->
+// 0.89.  R = 3 with calibration lines leaves two classes of S = 3, which
+// ran slower than unsplit (CG 6: 192 points 0.88 -> 1.17, 288 1.51 -> 1.54).
 Fold fold_of(const uint8_t* mask, int ny) {
   Fold best;
   for (int s = 1; s <= 3; ++s) {
@@ -52,76 +55,32 @@ Fold fold_of(const uint8_t* mask, int ny) {
   return best;
 }
 
-// out[col][c][y] = maps[col][c][y] W_ny^{rho y}
-__global__ void k_fold_maps(const float2* __restrict__ maps, float2* __restrict__ out, long total, int ny, int rho) {
-  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= total) return;
-  const int y = (int)(i % ny);
-  double s, c;
-  sincospi(-2.0 * (double)((long)rho * y % ny) / ny, &s, &c);
-  const double re = maps[i].x, im = maps[i].y;
-  out[i] = make_float2((float)(re * c - im * s), (float)(re * s + im * c));
-}
-
-// fully sampled classes (bit rho of full) as one Hermitian block per y' < N = ny / S:
-//   B[t][u] = g[t - u] sum_c conj(S_c[y' + t N]) S_c[y' + u N],
-//   g[d] = (1 / S) sum over the classes of exp(2 pi i rho d / S),
-// out [nx][high, low][S S][N]: per row t the real diagonal, then re and im of B[t][u],
-// u > t
-__global__ void k_fold_gram(const float2* __restrict__ maps, float* __restrict__ out, int nc, int ny, int nx, int S,
-                            unsigned full) {
-  const int N = ny / S, y = blockIdx.x * blockDim.x + threadIdx.x, col = blockIdx.y;
-  if (y >= N) return;
-  const float2* m = maps + (size_t)col * nc * ny + y;
-  float* o = out + (size_t)col * 2 * S * S * N + y;
-  auto put = [&](double v) {   // high word, low word
-    const float hi = (float)v;
-    o[0] = hi;
-    o[(size_t)S * S * N] = (float)(v - (double)hi);
-    o += N;
-  };
-  for (int t = 0; t < S; ++t)
-    for (int u = t; u < S; ++u) {
-      double gr = 0.0, gi = 0.0, re = 0.0, im = 0.0;
-      for (int rho = 0; rho < S; ++rho)
-        if ((full >> rho) & 1u) {
-          double s, c;
-          sincospi(2.0 * rho * (t - u) / S, &s, &c);
-          gr += c / S;
-          gi += s / S;
-        }
-      for (int c = 0; c < nc; ++c) {
-        const float2 a = m[(size_t)c * ny + t * N], b = m[(size_t)c * ny + u * N];
-        re += (double)a.x * b.x + (double)a.y * b.y;
-        im += (double)a.x * b.y - (double)a.y * b.x;
-      }
-      put(gr * re - gi * im);
-      if (u > t) put(gr * im + gi * re);
-    }
-}
-
-hipError_t build_fold(const Fold& f, const float2* maps, int nc, int ny, int nx, float2* fmaps, float* fgram,
-                      hipStream_t s) {
-  const long total = (long)nx * nc * ny;
-  if (f.split > 1)
-    for (int rho : f.part)
-      hipLaunchKernelGGL(k_fold_maps, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, maps, fmaps, total, ny, rho);
-  unsigned full = 0;
-  for (int rho : f.full) full |= 1u << rho;
-  if (full)
-    hipLaunchKernelGGL(k_fold_gram, dim3((ny / f.split + 63) / 64, nx), dim3(64), 0, s, maps, fgram, nc, ny, nx, f.split,
-                       full);
-  return hipGetLastError();
+double2 Fold::full_weight(int d) const {
+  const int at = part.empty() ? 0 : part[0];
+  double2 g = make_double2(0.0, 0.0);
+  for (int rho : full) {
+    const double ang = 2.0 * kPi * (double)((rho - at) * d % split) / split;
+    g.x += std::cos(ang) / split;
+    g.y += std::sin(ang) / split;
+  }
+  return g;
 }
 
 // ------------------------------------------------------------ map preparation
-// out[col][c][y] = (-1)^y sum_d Linv[c][d] maps[d][y][col]  (whitening, Sec. 2.1 Eq. (3))
+__device__ __forceinline__ void class_phase(int rho, int y, int ny, double& c, double& s) {   // W_ny^{rho y}
+  sincospi(-2.0 * (double)((long)rho * y % ny) / ny, &s, &c);
+}
+
+// out[col][c][y] = (-1)^y W_ny^{rho y} sum_d Linv[c][d] maps[d][y][col]  (whitening,
+// Sec. 2.1 Eq. (3); the factor of the split form, rounded once with the rest)
 __global__ void k_prep_maps_cart1d(const float2* __restrict__ maps, const double* __restrict__ linv,
-                                   float2* __restrict__ out, int nc, int ny, int nx) {
+                                   float2* __restrict__ out, int nc, int ny, int nx, int rho) {
   const int y = blockIdx.x * blockDim.x + threadIdx.x;
   const int col = blockIdx.y;
   if (y >= ny) return;
   const double sg = (y & 1) ? -1.0 : 1.0;
+  double pc = 1.0, ps = 0.0;
+  if (rho > 0) class_phase(rho, y, ny, pc, ps);
   for (int c = 0; c < nc; ++c) {
     double re = 0.0, im = 0.0;
     for (int d = 0; d <= c; ++d) {
@@ -130,14 +89,34 @@ __global__ void k_prep_maps_cart1d(const float2* __restrict__ maps, const double
       re += lr * m.x - li * m.y;
       im += lr * m.y + li * m.x;
     }
+    if (rho > 0) {
+      const double t = re * pc - im * ps;
+      im = re * ps + im * pc;
+      re = t;
+    }
     out[((size_t)col * nc + c) * ny + y] = make_float2((float)(sg * re), (float)(sg * im));
   }
 }
 
 hipError_t launch_prep_maps_cart1d(const float2* maps, const double* linv, float2* out, int nc,
-                                   int ny, int nx, hipStream_t s) {
+                                   int ny, int nx, int rho, hipStream_t s) {
   dim3 grid((ny + 63) / 64, nx), block(64);
-  hipLaunchKernelGGL(k_prep_maps_cart1d, grid, block, 0, s, maps, linv, out, nc, ny, nx);
+  hipLaunchKernelGGL(k_prep_maps_cart1d, grid, block, 0, s, maps, linv, out, nc, ny, nx, rho);
+  return hipGetLastError();
+}
+
+__global__ void k_phase_maps_cart1d(float2* __restrict__ maps, long total, int ny, int rho) {
+  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= total) return;
+  double c, s;
+  class_phase(rho, (int)(i % ny), ny, c, s);
+  const double re = maps[i].x, im = maps[i].y;
+  maps[i] = make_float2((float)(re * c - im * s), (float)(re * s + im * c));
+}
+
+hipError_t launch_phase_maps_cart1d(float2* maps, int nc, int ny, int nx, int rho, hipStream_t s) {
+  const long total = (long)nx * nc * ny;
+  hipLaunchKernelGGL(k_phase_maps_cart1d, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, maps, total, ny, rho);
   return hipGetLastError();
 }
 

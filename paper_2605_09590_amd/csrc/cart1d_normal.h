@@ -50,13 +50,16 @@ struct MaskLines {
   static constexpr bool kRegs = CF::kMaskInRegs;
   float w[kRegs ? CF::VB : 1];
   uint32_t bits = 0;
-  __device__ __forceinline__ void load(const float* __restrict__ maskw, int lane) {
+  // value r of the lane is line posB + shift (mod N)
+  __device__ __forceinline__ void load(const float* __restrict__ maskw, int lane, int shift = 0) {
     const bool inB = CF::inB(lane);
 #pragma unroll
     for (int r = 0; r < CF::VB; ++r) {
       // one batch of loads from in-bounds indices, zeroed by a factor (a
       // load under the lane condition gets a branch and a wait of its own)
-      const float m = maskw[inB ? CF::posB(lane, r) : 0] * (inB ? 1.f : 0.f);
+      int k = (inB ? CF::posB(lane, r) : 0) + shift;
+      k -= k >= CF::N ? CF::N : 0;
+      const float m = maskw[k] * (inB ? 1.f : 0.f);
       if constexpr (kRegs) w[r] = m;
       bits |= (m != 0.f ? 1u : 0u) << r;
     }
@@ -182,8 +185,11 @@ __global__ __launch_bounds__(64) void k_cart1d(Cart1dArgs a) {
 
   typename CF::Tw tw;
   CF::load_tw(tw, a.twt, lane);
+  // maps that carry W_N^{rho y} (split form, complex64): the right-hand side's noise
+  // goes into the transform rho lines lower, which gives the sum the same factor
+  const int shift = MODE == C1_PMR_RHS && !BF && a.rho > 0 ? a.rho : 0;
   MaskLines<CF> mk;
-  mk.load(a.maskw, lane);
+  mk.load(a.maskw, lane, shift);
 
   const size_t base = ((size_t)kk * a.nx + col) * N;
   const MS mcol = MS::of(a) + (size_t)col * a.nc * N;
@@ -201,7 +207,8 @@ __global__ __launch_bounds__(64) void k_cart1d(Cart1dArgs a) {
       float2 v[CF::VMAX];
 #pragma unroll
       for (int r = 0; r < VB; ++r) {
-        const int kc = CF::posB(lane, r);
+        int kc = CF::posB(lane, r) + shift;
+        kc -= kc >= N ? N : 0;
         if (mk.on(r)) {
           const uint32_t elem = (uint32_t)(((size_t)c * N + kc) * a.nx + col);
           const float2 n = draw_probe(arg_seed(a), arg_first(a) + kk, elem, 1u, 3);

@@ -10,22 +10,30 @@
 // classes partly sampled.  An empty class contributes nothing.  A fully sampled
 // one needs no transform: fold and unfold give
 //   q[y' + t ny/S] += sum_t' g[t - t'] (sum_c conj(S_c) S_c)(t, t') p[y' + t' ny/S],
-// an S x S Hermitian block per y' summed over the coils once per operator
-// (fgram).  Only partly sampled classes go through transforms, on maps that carry
-// W_ny^{rho y} (fmaps).  R = 2 with a calibration block is one 160-point pair per
+// an S x S Hermitian block per y'.  Only the partly sampled class goes through
+// transforms, and the operator's maps carry its phase W_ny^{rho y} (in the blocks it
+// turns g by a constant).  R = 2 with a calibration block is one 160-point pair per
 // coil instead of a 320-point one, and uniform sampling none.
 //
+// The blocks are not held in memory (8 S ny nx bytes beyond the operator's described
+// size): every workgroup sums its column's over the coils, in FP64, into the LDS that
+// the maps took.  With transforms the sums are taken from the staged maps as they
+// pass; the wavefronts of a workgroup share them.  Blocks held in memory and this, ms
+// (map of 20 CG iterations, K = 96, 12 coils, 128 columns): R = 2 + 24 lines 1.78 / 1.79
+// (320 points), 0.55 / 0.57 (64), uniform R = 2 0.98 / 1.06 and 0.26 / 0.29.  Summed by
+// every wavefront for itself, from memory, 320 x 320 x 15 with K = 256 took 1.08 times
+// as long as with held blocks (now 1.02).
+//
 // Layout: every per-probe field is stored column-major, [K][nx][ny], so a
-// column is one contiguous line; maps are [nx][nc][ny].  A workgroup is one
-// wavefront on 64 / LA probes of one image column, whose maps it stages through
-// LDS.  A transform of N = LA VA points runs as in colpass.h, in two register
+// column is one contiguous line; maps are [nx][nc][ny].  A wavefront works on 64 / LA
+// probes of one image column, whose maps it stages through LDS.  A transform of N = LA VA points runs as in colpass.h, in two register
 // steps with one LDS exchange, dealt to lanes as tasks: LA per probe in layout A
 // (points a + LA m), VA in layout B (frequencies k + VA r), where the forward and
 // inverse transforms meet in registers.
 //
 // Bound by the vector ALU (FP32, not packed) with the CG fields' traffic close
 // behind: 320 x 320 x 15 coils, R = 2 + 24 calibration lines, K = 256, one CG
-// iteration 0.53 ms (VALU 82 % busy; the eight fields read and written, 1.7 GB,
+// iteration 0.54 ms (VALU 82 % busy; the eight fields read and written, 1.7 GB,
 // take 0.36 ms at the copy rate) against 0.79 ms unsplit.
 #pragma once
 
@@ -37,16 +45,16 @@
 
 namespace pico {
 
-// probes per workgroup of one wavefront
+// probes per wavefront
 template <class CP> constexpr int kFoldProbes = 64 / CP::LA;
 
 // Map column of N values into an LDS buffer, straight from global memory (16
 // bytes per lane and instruction, no registers held; N even, so whole pairs);
-// wait_lds_loads() and a barrier come before the first read
+// wait_lds_loads() comes before the first read
 template <int N>
 __device__ __forceinline__ void stage_column(const float2* src, float2* dst) {
   wait_lds_reads();
-  const int lo = 2 * (int)threadIdx.x;
+  const int lo = 2 * (int)(threadIdx.x % 64);
 #pragma unroll
   for (int j = 0; j < N; j += 128)
     if (j + lo < N)
@@ -54,29 +62,71 @@ __device__ __forceinline__ void stage_column(const float2* src, float2* dst) {
                                        (__attribute__((address_space(3))) void*)(dst + j), 16, 0, 0);
 }
 
-template <class CP, int S, int MODE>
-__global__ __launch_bounds__(64, S * CP::VA <= 20 ? 3 : 2) void k_cart1d_split(Cart1dArgs a) {
+// FULL: 0 without a fully sampled class, else the wavefronts that share a workgroup's
+// blocks; TR: with a class to transform
+template <class CP, int S, int MODE, int FULL, bool TR>
+__global__ __launch_bounds__(64 * (FULL > 1 ? FULL : 1), S * CP::VA <= 20 && (FULL != 1 || !TR) ? 3 : 2) void k_cart1d_split(Cart1dArgs a) {
+  constexpr int NW = FULL > 1 ? FULL : 1;
   constexpr int LA = CP::LA, VA = CP::VA, N = CP::N, NY = N * S, G = kFoldProbes<CP>;
   static_assert(LA >= VA && LA <= 32, "layout B's tasks fit the lanes, their frequencies a word of mask bits");
   constexpr int STR = LA + 1, SPAN = VA * STR;   // exchange: Y[a][k] at k STR + a (STR odd: conflict-free)
   constexpr int V = S * VA;                      // column values per lane
   constexpr size_t EX = (size_t)G * SPAN * sizeof(float2), RED = 64 * 4 * sizeof(double);
-  __shared__ __attribute__((aligned(16))) char ex_raw[EX > RED ? EX : RED];
-  __shared__ __attribute__((aligned(16))) float2 maps[2 * NY];   // two deep
-  float2* ex = reinterpret_cast<float2*>(ex_raw);
-  double* red = reinterpret_cast<double*>(ex_raw);
-  const int tid = threadIdx.x, la = tid % LA, col = blockIdx.y;
-  const int k = blockIdx.x * G + tid / LA;
+  __shared__ __attribute__((aligned(16))) char ex_raw[NW][(EX > RED ? EX : RED) + 15 & ~15];
+  // two map columns a wavefront; then, in the first one's, the blocks: [high, low][S S][N] floats
+  __shared__ __attribute__((aligned(16))) float2 map_cols[NW][(S > 2 ? S : 2) * NY];
+  const int wave = NW > 1 ? threadIdx.x / 64 : 0, tid = NW > 1 ? threadIdx.x % 64 : threadIdx.x;
+  const int la = tid % LA, col = blockIdx.y, k0 = ((int)blockIdx.x * NW + wave) * G, k = k0 + tid / LA;
+  float2* ex = reinterpret_cast<float2*>(ex_raw[wave]);
+  double* red = reinterpret_cast<double*>(ex_raw[wave]);
+  float2* maps = map_cols[wave];
   const bool active = tid < G * LA && k < a.K;
   // layout B's task of this lane
   const int kb = tid % VA;
-  const bool activeB = tid < G * VA && (int)blockIdx.x * G + tid / VA < a.K;
+  const bool activeB = tid < G * VA && k0 + tid / VA < a.K;
   float2* exA = ex + tid / LA * SPAN + la;
   float2* exB = ex + tid / VA * SPAN + kb * STR;
 
-  const int nc = a.rho >= 0 ? a.nc : 0;   // coils to transform
-  auto stage = [&](int c) { stage_column<NY>(a.fmaps + ((size_t)col * a.nc + c) * NY, maps + (c & 1) * NY); };
+  const int nc = TR && a.rho >= 0 && k0 < a.K ? a.nc : 0;   // coils to transform
+  const float2* mcol = a.maps + (size_t)col * a.nc * NY;
+  auto stage = [&](int c) { stage_column<NY>(mcol + (size_t)c * NY, maps + (c & 1) * NY); };
   if (nc > 0) stage(0);
+
+  // fully sampled classes: block of y' = y, per row t the real diagonal, then re and im
+  // of the columns u > t, summed over the coils for RB values of y per thread: from the
+  // staged maps, or from memory where no coil is staged (C coils' loads at once, the
+  // first ones' ahead of the CG fields if none is)
+  constexpr int T = 64 * NW, RB = (N + T - 1) / T, C = S * RB > 6 ? 2 : S * RB > 3 ? 4 : 8;
+  double blk[RB][S * S];
+#pragma unroll
+  for (int r = 0; r < RB; ++r)
+#pragma unroll
+    for (int j = 0; j < S * S; ++j) blk[r][j] = 0.0;
+  auto block_add = [](double (&b)[S * S], const float2 (&m)[S]) {
+    int j = 0;
+#pragma unroll
+    for (int t = 0; t < S; ++t) {
+      const double x = m[t].x, y = m[t].y;
+      b[j++] += x * x + y * y;
+#pragma unroll
+      for (int u = t + 1; u < S; ++u, j += 2) {
+        b[j] += x * m[u].x + y * m[u].y;
+        b[j + 1] += x * m[u].y - y * m[u].x;
+      }
+    }
+  };
+
+  float2 bm[C][RB][S];
+  auto block_maps = [&](int c0) {   // in-bounds loads on every lane; a coil past the last is not used
+#pragma unroll
+    for (int h = 0; h < C; ++h)
+#pragma unroll
+      for (int r = 0; r < RB; ++r)
+#pragma unroll
+        for (int t = 0; t < S; ++t)
+          bm[h][r][t] = mcol[(size_t)min(c0 + h, a.nc - 1) * NY + t * N + min((int)threadIdx.x + T * r, N - 1)];
+  };
+  if constexpr (FULL && !TR) block_maps(0);
 
   float2 tw[VA];
 #pragma unroll
@@ -149,7 +199,7 @@ __global__ __launch_bounds__(64, S * CP::VA <= 20 ? 3 : 2) void k_cart1d_split(C
 #pragma unroll
   for (int i = 0; i < V; ++i) qa[i] = make_float2(0.f, 0.f);
   wait_lds_loads();
-  __syncthreads();
+  wave_sync();
   int on = 0;   // sampled frequencies of layout B's task
   if (nc > 0) {
 #pragma unroll
@@ -158,6 +208,17 @@ __global__ __launch_bounds__(64, S * CP::VA <= 20 ? 3 : 2) void k_cart1d_split(C
   for (int c = 0; c < nc; ++c) {
     if (c + 1 < nc) stage(c + 1);   // the buffer of map c - 1, whose last use is behind
     const float2* mv = maps + (c & 1) * NY;
+    if constexpr (FULL) {
+#pragma unroll
+      for (int r = 0; r < RB; ++r) {
+        const int y = (int)threadIdx.x + T * r;
+        if (y >= N) break;
+        float2 m[S];
+#pragma unroll
+        for (int t = 0; t < S; ++t) m[t] = mv[t * N + y];
+        block_add(blk[r], m);
+      }
+    }
     asm volatile("" : "+v"(on));   // opaque: LA unpacked masks held over the loop would spill
     if (active) {
       float2 z[VA];
@@ -171,7 +232,7 @@ __global__ __launch_bounds__(64, S * CP::VA <= 20 ? 3 : 2) void k_cart1d_split(C
 #pragma unroll
       for (int j = 0; j < VA; ++j) exA[j * STR] = j ? cmul(z[j], tw[j]) : z[j];
     }
-    __syncthreads();
+    wave_sync();
     if (activeB) {
       float2 b[LA];
 #pragma unroll
@@ -188,7 +249,7 @@ __global__ __launch_bounds__(64, S * CP::VA <= 20 ? 3 : 2) void k_cart1d_split(C
       for (int i = 0; i < LA; ++i) exB[i] = b[i];   // the task's own values
     }
     wait_lds_loads();
-    __syncthreads();
+    wave_sync();
     if (active) {
       float2 z[VA];
 #pragma unroll
@@ -199,26 +260,65 @@ __global__ __launch_bounds__(64, S * CP::VA <= 20 ? 3 : 2) void k_cart1d_split(C
     }
   }
 
+  if constexpr (FULL) {
+    if (nc == 0) {
+      for (int c0 = 0; c0 < a.nc; c0 += C) {
+        if (TR || c0 > 0) block_maps(c0);
+#pragma unroll
+        for (int h = 0; h < C; ++h) {
+          if (c0 + h >= a.nc) break;
+#pragma unroll
+          for (int r = 0; r < RB; ++r) block_add(blk[r], bm[h][r]);
+        }
+      }
+    }
+    __syncthreads();   // every wavefront is done with its maps
+    float* blocks = reinterpret_cast<float*>(map_cols[0]);
+#pragma unroll
+    for (int r = 0; r < RB; ++r) {
+      const int y = (int)threadIdx.x + T * r;
+      if (y >= N) break;
+      int j = 0;
+      auto put = [&](double v) {
+        const float hi = (float)v;
+        blocks[j * N + y] = hi;
+        blocks[(S * S + j) * N + y] = (float)(v - (double)hi);
+        ++j;
+      };
+#pragma unroll
+      for (int t = 0; t < S; ++t) {
+        put(a.full[0].x * blk[r][j]);
+#pragma unroll
+        for (int u = t + 1; u < S; ++u) {   // t - u < 0: the conjugate of the weight at u - t
+          const double2 g = a.full[u - t];
+          const double re = blk[r][j], im = blk[r][j + 1];
+          put(g.x * re + g.y * im);
+          put(g.x * im - g.y * re);
+        }
+      }
+    }
+    __syncthreads();
+  }
   if (active) {
     // q = lam p + transforms / ny + the fully sampled classes
     constexpr float inv = 1.0f / NY;
 #pragma unroll
     for (int i = 0; i < V; ++i) qa[i] = cfma(cscale(qa[i], inv), a.lam, pv[i]);
-    if (a.fgram) {
+    if constexpr (FULL) {
       // blocks as high and low words: one rounded block per pixel would not
       // average out as the transforms' errors do (FP64 products spill)
 #pragma unroll
       for (int m = 0; m < VA; ++m)
 #pragma unroll
         for (int w = 1; w >= 0; --w) {
-          const float* b = a.fgram + ((size_t)col * 2 + w) * (S * S) * N + la + LA * m;
+          const float* b = reinterpret_cast<float*>(map_cols[0]) + w * (S * S) * N + la + LA * m;
           int j = 0;
 #pragma unroll
           for (int t = 0; t < S; ++t) {
-            qa[t * VA + m] = cfma(qa[t * VA + m], b[(size_t)j++ * N], pv[t * VA + m]);
+            qa[t * VA + m] = cfma(qa[t * VA + m], b[j++ * N], pv[t * VA + m]);
 #pragma unroll
             for (int u = t + 1; u < S; ++u) {   // B[t][u] and its conjugate B[u][t]
-              const float2 g = make_float2(b[(size_t)j * N], b[(size_t)(j + 1) * N]);
+              const float2 g = make_float2(b[j * N], b[(j + 1) * N]);
               j += 2;
               qa[t * VA + m] = cadd(qa[t * VA + m], cmul(g, pv[u * VA + m]));
               qa[u * VA + m] = cadd(qa[u * VA + m], cmulc(g, pv[t * VA + m]));
@@ -245,10 +345,10 @@ __global__ __launch_bounds__(64, S * CP::VA <= 20 ? 3 : 2) void k_cart1d_split(C
     }
   }
   // sums over the probe's LA lanes, each in lane order
-  __syncthreads();
+  wave_sync();
 #pragma unroll
   for (int j = 0; j < 4; ++j) red[tid * 4 + j] = d[j];
-  __syncthreads();
+  wave_sync();
   if (active && la < 4) {
     double s = 0.0;
     for (int i = 0; i < LA; ++i) s += red[(tid - la + i) * 4 + la];
@@ -257,18 +357,34 @@ __global__ __launch_bounds__(64, S * CP::VA <= 20 ? 3 : 2) void k_cart1d_split(C
 }
 
 // ------------------------------------------------------------ dispatch
-template <int S, class CP>
-static hipError_t split_launch(int mode, const Cart1dArgs& a, hipStream_t s) {
-  constexpr int G = kFoldProbes<CP>;
-  const dim3 grid((a.K + G - 1) / G, a.nx), block(64);
+// Wavefronts that share a column's blocks: as many as have rows of them (64 each), up to
+// what fits 64 KiB of LDS
+template <class CP, int S>
+constexpr int kBlockWaves = CP::N <= 64 ? 1 : CP::N <= 128 ? 2 :
+    (kFoldProbes<CP> * CP::VA * (CP::LA + 1) + (S > 2 ? S : 2) * S * CP::N) * 8 * 4 <= 64 * 1024 ? 4 : 2;
+
+template <int S, class CP, int FULL, bool TR>
+static hipError_t split_modes(int mode, const Cart1dArgs& a, hipStream_t s) {
+  constexpr int NW = FULL > 1 ? FULL : 1, G = kFoldProbes<CP> * NW;
+  const dim3 grid((a.K + G - 1) / G, a.nx), block(64 * NW);
   switch (mode) {
-    case C1_FIRST_PROBE: hipLaunchKernelGGL((k_cart1d_split<CP, S, C1_FIRST_PROBE>), grid, block, 0, s, a); break;
-    case C1_FIRST_BUF: hipLaunchKernelGGL((k_cart1d_split<CP, S, C1_FIRST_BUF>), grid, block, 0, s, a); break;
-    case C1_ITER: hipLaunchKernelGGL((k_cart1d_split<CP, S, C1_ITER>), grid, block, 0, s, a); break;
-    case C1_APPLY: hipLaunchKernelGGL((k_cart1d_split<CP, S, C1_APPLY>), grid, block, 0, s, a); break;
+    case C1_FIRST_PROBE: hipLaunchKernelGGL((k_cart1d_split<CP, S, C1_FIRST_PROBE, FULL, TR>), grid, block, 0, s, a); break;
+    case C1_FIRST_BUF: hipLaunchKernelGGL((k_cart1d_split<CP, S, C1_FIRST_BUF, FULL, TR>), grid, block, 0, s, a); break;
+    case C1_ITER: hipLaunchKernelGGL((k_cart1d_split<CP, S, C1_ITER, FULL, TR>), grid, block, 0, s, a); break;
+    case C1_APPLY: hipLaunchKernelGGL((k_cart1d_split<CP, S, C1_APPLY, FULL, TR>), grid, block, 0, s, a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
+}
+
+template <int S, class CP>
+static hipError_t split_launch(int mode, const Cart1dArgs& a, hipStream_t s) {
+  constexpr int NW = kBlockWaves<CP, S>;
+  if (a.full[0].x == 0.0) return split_modes<S, CP, 0, true>(mode, a, s);
+  const bool share = a.K > kFoldProbes<CP> * (NW - 1);   // a workgroup's wavefronts all have probes
+  if (a.rho < 0) return share ? split_modes<S, CP, NW, false>(mode, a, s) : split_modes<S, CP, 1, false>(mode, a, s);
+  if constexpr (S > 1) return share ? split_modes<S, CP, NW, true>(mode, a, s) : split_modes<S, CP, 1, true>(mode, a, s);
+  return hipErrorInvalidValue;   // S = 1 has a single class
 }
 
 }  // namespace pico

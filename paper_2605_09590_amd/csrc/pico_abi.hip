@@ -94,8 +94,7 @@ struct pico_op_s {
   bool stream_bf = false;     // grid path: row-transformed planes T kept as bfloat16
   float* maskw = nullptr;     // separable path: [ny] mask[k] / ny
   int split = 1, rho = -1;    // separable path, column transforms: see cart1d_split.h
-  float2* fmaps = nullptr;
-  float* fgram = nullptr;     // NULL: no fully sampled class
+  double2 full[3] = {};
   bool use_gram = false;      // separable path: dense per-column blocks on the matrix cores
   float2* gram = nullptr;     // [nx][ny][ny] conj(M_x[i][j]) at [x][j][i]
   double2* gram_c = nullptr;  // [ny] circulant c(d) (build input)
@@ -316,8 +315,7 @@ hipError_t launch_normal(pico_op_t op, int K, int mode, const NormalCall& c, hip
     a.maskw = op->maskw;
     a.split = op->split;
     a.rho = op->rho;
-    a.fmaps = op->split > 1 ? op->fmaps : op->maps;
-    a.fgram = op->fgram;
+    for (int d = 0; d < 3; ++d) a.full[d] = op->full[d];
     a.twt = op->twt;
     a.src = c.src;
     a.x = op->x;
@@ -1039,26 +1037,18 @@ pico_status_t pico::init_in_arena(const pico_op_desc_t* d, void* stream, pico::D
     std::vector<float2> tw = twiddle_table(ny);
     if ((e = hipMemcpyAsync(op->maskw, w.data(), ny * sizeof(float), hipMemcpyHostToDevice, s)) != hipSuccess) return bad(e, "upload");
     if ((e = hipMemcpyAsync(op->twt, tw.data(), ny * sizeof(float2), hipMemcpyHostToDevice, s)) != hipSuccess) return bad(e, "upload");
-    if ((e = pico::launch_prep_maps_cart1d((const float2*)d->maps, linv_d, op->maps, nc, ny, nx, s)) != hipSuccess) return bad(e, "prep maps");
-    if (op->maps_bf && (e = pico::launch_quantise_maps(op->maps, op->maps_bf, (long)(n * nc), true, s)) != hipSuccess) return bad(e, "bfloat16 maps");
-    if (!wants_gram(d) && !wants_gram16(d)) op->rho = 0;   // unsplit: one class of all frequencies
+    // column transforms: the split form that the mask alone decides; its partly sampled
+    // class's phase goes into the maps (bfloat16 storage: after their rounding)
     if (!wants_gram(d) && !wants_gram16(d)) {
-      // the split form's buffers are beyond the described bytes: with no room for
-      // them (they are not counted) the operator runs unsplit
-      float* fg = nullptr;
-      const size_t held = op->bytes, top = op->peak;
-      const bool room = op->alloc(&op->fmaps, n * nc) == hipSuccess && op->alloc(&fg, 6 * n) == hipSuccess;
-      op->bytes = held;
-      op->peak = top;
-      if (!room) (void)hipGetLastError();
-      if (room) {
       const pico::Fold f = pico::fold_of(mask_h.data(), ny);
       op->split = f.split;
-      op->rho = f.part.empty() ? -1 : f.part[0];
-      if (!f.full.empty()) op->fgram = fg;
-      if ((e = pico::build_fold(f, op->maps, nc, ny, nx, op->fmaps, op->fgram, s)) != hipSuccess) return bad(e, "class maps");
-      }
+      op->rho = f.rho();
+      for (int i = 0; i < f.split; ++i) op->full[i] = f.full_weight(i);
     }
+    const int turn = op->rho > 0 ? op->rho : 0;
+    if ((e = pico::launch_prep_maps_cart1d((const float2*)d->maps, linv_d, op->maps, nc, ny, nx, op->maps_bf ? 0 : turn, s)) != hipSuccess) return bad(e, "prep maps");
+    if (op->maps_bf && (e = pico::launch_quantise_maps(op->maps, op->maps_bf, (long)(n * nc), true, s)) != hipSuccess) return bad(e, "bfloat16 maps");
+    if (op->maps_bf && turn && (e = pico::launch_phase_maps_cart1d(op->maps, nc, ny, nx, turn, s)) != hipSuccess) return bad(e, "class maps");
     if (wants_gram(d)) {
       if ((e = op->alloc(&op->gram, pico::gram_bytes(ny, nx) / sizeof(float2))) != hipSuccess) return bad(e, "dense blocks");
       if ((e = op->alloc(&op->gram_c, ny)) != hipSuccess) return bad(e, "dense blocks");

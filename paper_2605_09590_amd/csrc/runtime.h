@@ -39,13 +39,12 @@ enum Cart1dMode : int {
 
 struct Cart1dArgs {
   int ny, nx, nc, K;           // K probes in this launch
-  const float2* maps;          // [nx][nc][ny] whitened, (-1)^y folded
-  const uint32_t* maps_bf;     // the same maps as packed bfloat16 pairs, or NULL
+  const float2* maps;          // [nx][nc][ny] whitened, (-1)^y folded, times W_ny^{rho y} (rho > 0)
+  const uint32_t* maps_bf;     // the same maps without that factor, as packed bfloat16 pairs, or NULL
   const float* maskw;          // [ny] weight mask[k] / ny (0 off the mask)
   int split;                   // split factor S (cart1d_split.h)
   int rho;                     // the partly sampled class, or -1
-  const float2* fmaps;         // [nx][nc][ny] maps times W_ny^{rho y}
-  const float* fgram;          // [nx][high, low][S S][ny / S] fully sampled classes, or NULL
+  double2 full[3];             // fully sampled classes: Fold::full_weight, or zeros
   const float2* twt;           // [ny] W_ny^m = exp(-2 pi i m / ny)
   const float2* src;           // input field   (mode dependent)
   float2* x;                   // [K][nx][ny]
@@ -320,15 +319,17 @@ hipError_t launch_cart1d_split3(int mode, const Cart1dArgs& a, hipStream_t s);
 // 0.81 -> 0.83, 192 and 288 equal, 320 1.50 -> 1.59, 512 2.23 -> 2.70)
 constexpr bool unsplit_in_split_kernel(int ny) { return ny == 96 || ny == 256 || ny == 384; }
 // split of a phase-encode mask's frequencies into classes k = rho (mod split):
-// the fully and the partly sampled ones
+// the fully and the partly sampled ones (at most one of these)
 struct Fold {
   int split = 1;
   std::vector<int> full, part;
+  int rho() const { return part.empty() ? -1 : part[0]; }
+  // (1 / split) sum over the full classes of exp(2 pi i (class - rho) d / split), d <
+  // split (rho 0 without a partly sampled class): what couples values d ny / split
+  // apart, on maps that carry W_ny^{rho y}
+  double2 full_weight(int d) const;
 };
 Fold fold_of(const uint8_t* mask, int ny);
-// fmaps [nx][nc][ny] (split > 1), fgram [nx][2][split^2][ny / split]
-hipError_t build_fold(const Fold& f, const float2* maps, int nc, int ny, int nx, float2* fmaps, float* fgram,
-                      hipStream_t s);
 // dense per-column normal operator (phase-encode masks, FP32 matrix cores)
 bool gram_supported(int ny);
 size_t gram_bytes(int ny, int nx);
@@ -347,8 +348,11 @@ hipError_t launch_set_tile(uint64_t* tp, uint64_t seed, uint64_t first, hipStrea
 hipError_t launch_final_x(const FinalArgs& a, hipStream_t s);
 hipError_t launch_scalars(const ScalarArgs& a, hipStream_t s);
 hipError_t launch_accum_colmajor(const AccumArgs& a, hipStream_t s);
+// out times W_ny^{rho y} (rho >= 0)
 hipError_t launch_prep_maps_cart1d(const float2* maps, const double* linv, float2* out,
-                                   int nc, int ny, int nx, hipStream_t s);
+                                   int nc, int ny, int nx, int rho, hipStream_t s);
+// maps [nx][nc][ny] times W_ny^{rho y}, in place
+hipError_t launch_phase_maps_cart1d(float2* maps, int nc, int ny, int nx, int rho, hipStream_t s);
 hipError_t launch_transpose_in(const float2* v, float2* out, int K, int ny, int nx, hipStream_t s);
 hipError_t launch_transpose_out(const float2* x, float2* u, int K, int ny, int nx, hipStream_t s);
 hipError_t launch_finalize(const double* sum, double* var, int64_t n, double inv_count,
