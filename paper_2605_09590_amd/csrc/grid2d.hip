@@ -332,12 +332,12 @@ hipError_t launch_prep_maps_rowmajor(const float2* maps, const double* linv, flo
   return hipGetLastError();
 }
 
-// w[ky][kx] = mask[ky][kx] * scale (Cartesian 2-D weights)
+// w[ky][kx] (by_column: w[kx][ky]) = mask[ky][kx] * scale (Cartesian 2-D weights)
 __global__ void k_mask_weights(const uint8_t* __restrict__ mask, float* __restrict__ w, int ny, int nx,
-                               float scale) {
+                               float scale, int by_column) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= ny * nx) return;
-  w[i] = mask[i] ? scale : 0.f;
+  w[by_column ? (size_t)(i % nx) * ny + i / nx : (size_t)i] = mask[i] ? scale : 0.f;
 }
 
 __global__ void k_quantise_maps(float2* __restrict__ maps, uint32_t* __restrict__ bf, long count, int round_copy) {
@@ -354,10 +354,10 @@ hipError_t launch_quantise_maps(float2* maps, uint32_t* bf, long count, bool rou
   return hipGetLastError();
 }
 
-hipError_t launch_mask_weights(const uint8_t* mask, float* w, int ny, int nx, float scale,
+hipError_t launch_mask_weights(const uint8_t* mask, float* w, int ny, int nx, float scale, bool by_column,
                                hipStream_t s) {
   hipLaunchKernelGGL(k_mask_weights, dim3((ny * nx + 255) / 256), dim3(256), 0, s, mask, w, ny, nx,
-                     scale);
+                     scale, by_column ? 1 : 0);
   return hipGetLastError();
 }
 

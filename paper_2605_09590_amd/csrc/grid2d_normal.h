@@ -312,15 +312,9 @@ __global__ __launch_bounds__(64 * NW) void k_rows_fwd(Grid2dArgs a) {
 // ---------------------------------------------------------------- column pass
 // Unpadded 320-point columns are held to 128 registers (8 values spilled): three
 // workgroups of five wavefronts share a CU instead of two (solves of 96 probes, 16
-// coils: complex64 23.3 -> 23.1 ms, bfloat16 planes 19.7 -> 17.5 ms).  Padded ones
-// need 200 and spill 32 at 168: left alone (20.9 ms against 28.8).
+// coils: complex64 23.3 -> 23.1 ms, bfloat16 planes 19.7 -> 17.5 ms).
 template <class CP, bool PAD>
 constexpr int kColWaves = CP::N == 320 && !PAD ? 4 : 1;
-// Padded 288-point columns run 24 x 12 points (six wavefronts and fewer registers in
-// place of five with 190: 18.0 -> 17.2 ms, 12 coils, 48 probes); 32 x 10 and 32 x 12
-// were slower at 320 and 384 points (20.9 / 22.3, 13.8 / 14.2 ms).
-template <class CP>
-using PadPlan = std::conditional_t<CP::N == 288, ColPlan<24, 12>, CP>;
 
 // Per column of a (k, c) plane: transform along y, weights, inverse transform,
 // in place.  PAD (the Toeplitz grids, Gy = 2 ny): the column is the first half
@@ -402,6 +396,79 @@ __global__ __launch_bounds__(CP::THREADS, (kColWaves<CP, PAD>)) void k_cols(Grid
 #pragma unroll
     for (int m = 0; m < VA; ++m) narrow(pl[(size_t)(t + LA * m) * a.Gx], out[m]);
   }
+}
+
+// The same through an LDS tile, for the lengths of staged_cols: 256 / L adjacent columns
+// of a plane are loaded (batches of 8 loads per thread), transformed as lines of Gy
+// points by groups of L lanes, a column each, and stored.  PAD: both layouts place
+// values m < VA / 2 and r < VB / 2 in the first half, so the zeros and the unused
+// outputs fold out of the first and last steps.  a.w is [Gx][Gy].
+// The register form holds three sets of VA values at once when PAD (x, out and the
+// twiddles: 190-200 registers at 288 and 320 points) and 32 values a task at 512, so
+// few wavefronts are left to hide its loads.  Maps of 12 coils, 8 CG iterations, 0.9 GB
+// of planes, ms, registers / tile: padded 288 points 9.30 / 8.40 (bfloat16 planes 8.24 /
+// 7.21), 320 9.44 / 8.09 (8.21 / 7.22), unpadded 512 7.64 / 6.95 (6.18 / 5.96); the
+// others are as fast or faster in registers: padded 256 6.58 / 7.43 (5.65 / 6.58), 384
+// 9.49 / 9.39 (7.73 / 8.16), unpadded 576 9.00 / 8.98 (6.44 / 6.51), 640 9.32 / 9.27
+// (6.52 / 6.57), 768 8.78 / 8.86 (6.23 / 7.17).
+template <class CF, bool TB, bool PAD>
+__global__ __launch_bounds__(256) void k_cols_staged(Grid2dArgs a) {
+  constexpr int L = CF::L, NC = 256 / L, VA = CF::VA, VB = CF::VB, TS = NC + 1, B = 8;
+  constexpr int NY = PAD ? CF::N / 2 : CF::N, TOTAL = NY * NC;
+  static_assert(64 % L == 0, "a group stays within its wavefront");
+  static_assert(!PAD || (VA % 2 == 0 && VB % 2 == 0), "halves of a lane's values");
+  static_assert(TOTAL % 256 == 0, "whole rounds of loads");
+  using E = std::conditional_t<TB, uint32_t, float2>;
+  extern __shared__ float2 dyn[];   // [NY][TS] tile; between the loads and the stores, the groups' exchanges
+  const int S = a.Gx / NC;
+  const long vb = strip_of(blockIdx.x, (long)S * a.K * a.nc);
+  if (vb < 0) return;
+  const int x0 = (int)(vb % S) * NC, g = threadIdx.x / L, lane = threadIdx.x % L;
+  E* __restrict__ pl;
+  if constexpr (TB) pl = a.Tb;
+  else pl = a.T;
+  pl += (size_t)(vb / S) * NY * a.Gx + x0;
+#pragma unroll
+  for (int i0 = 0; i0 < TOTAL; i0 += B * 256) {
+    E v[B];
+#pragma unroll
+    for (int u = 0; u < B; ++u) {
+      const int i = i0 + u * 256 + (int)threadIdx.x;
+      if (i0 + u * 256 < TOTAL) v[u] = pl[(size_t)(i / NC) * a.Gx + i % NC];
+    }
+#pragma unroll
+    for (int u = 0; u < B; ++u) {
+      const int i = i0 + u * 256 + (int)threadIdx.x;
+      if (i0 + u * 256 < TOTAL) dyn[i / NC * TS + i % NC] = widen(v[u]);
+    }
+  }
+  __syncthreads();
+  const bool inA = CF::inA(lane), inB = CF::inB(lane);
+  typename CF::Tw tw;
+  CF::load_tw(tw, a.twy, lane);
+  float2 v[CF::VMAX];
+#pragma unroll
+  for (int m = 0; m < VA; ++m) {
+    if (PAD && m >= VA / 2) v[m] = make_float2(0.f, 0.f);
+    else v[m] = inA ? dyn[CF::posA(lane, m) * TS + g] : make_float2(0.f, 0.f);
+  }
+  __syncthreads();
+  float2* ex = dyn + g * CF::SPAN;
+  CF::template forward<false>(v, ex, lane, tw);
+  const float* __restrict__ w = a.w + (size_t)(x0 + g) * a.Gy;
+  if (inB) {
+#pragma unroll
+    for (int r = 0; r < VB; ++r) v[r] = cscale(v[r], w[CF::posB(lane, r)]);
+  }
+  CF::template inverse<true>(v, ex, lane, tw);
+  __syncthreads();
+  if (inA) {
+#pragma unroll
+    for (int m = 0; m < (PAD ? VA / 2 : VA); ++m) dyn[CF::posA(lane, m) * TS + g] = v[m];
+  }
+  __syncthreads();
+#pragma unroll 8
+  for (int i = threadIdx.x; i < TOTAL; i += 256) narrow(pl[(size_t)(i / NC) * a.Gx + i % NC], dyn[i / NC * TS + i % NC]);
 }
 
 // ---------------------------------------------------------------- row pass 2
@@ -684,19 +751,42 @@ static hipError_t cols(const Grid2dArgs& a, hipStream_t s) {
 }
 
 
+template <class CF, bool TB, bool PAD>
+static hipError_t cols_staged(const Grid2dArgs& a, hipStream_t s) {
+  constexpr int NC = 256 / CF::L, NY = PAD ? CF::N / 2 : CF::N;
+  static const hipError_t attr = allow_lds((const void*)k_cols_staged<CF, TB, PAD>);
+  if (attr != hipSuccess) return attr;
+  constexpr size_t lds = std::max((size_t)NY * (NC + 1), (size_t)NC * CF::SPAN) * sizeof(float2);
+  static_assert(lds <= 160 * 1024, "fits the LDS");
+  const long W = (long)(a.Gx / NC) * a.K * a.nc;
+  hipLaunchKernelGGL((k_cols_staged<CF, TB, PAD>), dim3(strip_grid(W)), dim3(256), lds, s, a);
+  return hipGetLastError();
+}
+
 // One application of the normal operator (three passes) with storage ST:
 // 0 complex64, 1 bfloat16 maps, 2 bfloat16 maps and planes
 template <int ST>
 static hipError_t grid_passes(int mode, const Grid2dArgs& a, hipStream_t s) {
   hipError_t e = with_line(a.Gx, [&](auto cf) { return rows_fwd<decltype(cf), ST>(mode, a, s); });
   if (e != hipSuccess) return e;
-  e = with_col(a.ny, [&](auto cp) {
+  if (staged_cols(a.ny, a.Gy == 2 * a.ny)) {
+    e = with_line(a.Gy, [&](auto cf) {
+      using CF = decltype(cf);
+      if constexpr (staged_cols(CF::N / 2, true)) {
+        if (a.Gy == 2 * a.ny) return cols_staged<CF, ST == 2, true>(a, s);
+      }
+      if constexpr (staged_cols(CF::N, false)) {
+        if (a.Gy == a.ny) return cols_staged<CF, ST == 2, false>(a, s);
+      }
+      return hipErrorInvalidValue;
+    });
+  } else e = with_col(a.ny, [&](auto cp) {
     using CP = decltype(cp);
     // padded lines have 64 to 768 points, unpadded ones (2-D masks) too
-    if constexpr (CP::N <= 384) {
-      if (a.Gy == 2 * a.ny) return cols<PadPlan<CP>, ST == 2, true>(a, s);
+    if constexpr (CP::N <= 384 && !staged_cols(CP::N, true)) {
+      if (a.Gy == 2 * a.ny) return cols<CP, ST == 2, true>(a, s);
     }
-    if constexpr (CP::N >= 64 && CP::N != 80 && CP::N != 144) {
+    if constexpr (CP::N >= 64 && CP::N != 80 && CP::N != 144 && !staged_cols(CP::N, false)) {
       if (a.Gy == a.ny) return cols<CP, ST == 2, false>(a, s);
     }
     return hipErrorInvalidValue;

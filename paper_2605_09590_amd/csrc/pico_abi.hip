@@ -1078,6 +1078,7 @@ pico_status_t pico::init_in_arena(const pico_op_desc_t* d, void* stream, pico::D
       if ((e = hipMemcpyAsync(op->twx, tx.data(), Gx * sizeof(float2), hipMemcpyHostToDevice, s)) != hipSuccess) return bad(e, "upload");
       if ((e = hipMemcpyAsync(op->twy, ty.data(), Gy * sizeof(float2), hipMemcpyHostToDevice, s)) != hipSuccess) return bad(e, "upload");
     }
+    const bool by_column = pico::staged_cols(ny, Gy == 2 * ny);   // layout of the weights
     const int fold = d->sampling == PICO_CART_2D;
     if ((e = pico::launch_prep_maps_rowmajor((const float2*)d->maps, linv_d, op->maps, nc, ny, nx, fold, s)) != hipSuccess) return bad(e, "prep maps");
     // CG-SENSE: the rounded maps define the operator on every path (the FP32
@@ -1087,12 +1088,12 @@ pico_status_t pico::init_in_arena(const pico_op_desc_t* d, void* stream, pico::D
     // probes keep the unrounded maps.
     if (op->maps_bf && (e = pico::launch_quantise_maps(op->maps, op->maps_bf, (long)(n * nc), d->recon == PICO_CGSENSE, s)) != hipSuccess) return bad(e, "bfloat16 maps");
     if (d->sampling == PICO_CART_2D) {
-      if ((e = pico::launch_mask_weights(d->mask, op->w, ny, nx, (float)(1.0 / ((double)ny * nx)), s)) != hipSuccess) return bad(e, "weights");
+      if ((e = pico::launch_mask_weights(d->mask, op->w, ny, nx, (float)(1.0 / ((double)ny * nx)), by_column, s)) != hipSuccess) return bad(e, "weights");
     } else {
       if (!op->kb_normal) {
         char* tscratch = nullptr;
         if ((e = op->alloc(&tscratch, pico::toeplitz_scratch_bytes(d->nsamples, ny, nx))) != hipSuccess) return bad(e, "Toeplitz scratch");
-        if ((e = pico::build_toeplitz_weights(d->traj, d->nsamples, ny, nx, op->w, tscratch, s)) != hipSuccess) return bad(e, "Toeplitz weights");
+        if ((e = pico::build_toeplitz_weights(d->traj, d->nsamples, ny, nx, op->w, by_column, tscratch, s)) != hipSuccess) return bad(e, "Toeplitz weights");
         op->release(tscratch);
       }
       if (d->kb_width > 0) {

@@ -100,7 +100,8 @@ struct Grid2dArgs {
   int ny, nx, nc, K, Gy, Gx;
   const float2* maps;          // [nc][ny][nx] whitened (and sign-folded for Cartesian)
   const uint32_t* maps_bf;     // the same maps as packed bfloat16 pairs, or NULL
-  const float* w;              // [Gy][Gx] real weights (Toeplitz: even ky first, then odd)
+  const float* w;              // [Gy][Gx] real weights (Toeplitz: even ky first, then odd), or
+                               // [Gx][Gy] in order (staged_cols)
   const float2* twx;           // [Gx] W_Gx^m
   const float2* twy;           // [Gy] W_Gy^m
   float2* T;                   // [K][nc][ny][Gx] row-transformed planes
@@ -121,6 +122,11 @@ struct Grid2dArgs {
   int k0;                      // probes of the call before this launch's first
 };
 
+// Grid columns of ny points (pad: as the first half of lines of 2 ny) that go through
+// an LDS tile (k_cols_staged) instead of straight through registers (k_cols): the
+// lengths where that is faster (see k_cols_staged)
+constexpr bool staged_cols(int ny, bool pad) { return pad ? ny == 288 || ny == 320 : ny == 512; }
+
 bool cart1d_supported(int ny);
 bool grid_line_supported(int n);
 hipError_t launch_grid_normal(int mode, const Grid2dArgs& a, hipStream_t s);
@@ -128,7 +134,7 @@ hipError_t launch_grid_normal_bf16(int mode, const Grid2dArgs& a, hipStream_t s)
 hipError_t launch_accum_rowmajor(const AccumArgs& a, hipStream_t s);
 hipError_t launch_prep_maps_rowmajor(const float2* maps, const double* linv, float2* out, int nc,
                                      int ny, int nx, int fold, hipStream_t s);
-hipError_t launch_mask_weights(const uint8_t* mask, float* w, int ny, int nx, float scale,
+hipError_t launch_mask_weights(const uint8_t* mask, float* w, int ny, int nx, float scale, bool by_column,
                                hipStream_t s);
 // bf = maps rounded to bfloat16 (nearest even); round_copy: maps too become
 // the rounded values (the FP32 copy then describes the same operator)
@@ -174,7 +180,7 @@ hipError_t launch_accum_abs2(const float2* u, double* sum, double* sum_im, doubl
 hipError_t launch_fill_zero(float2* a, long total, hipStream_t s);
 size_t toeplitz_scratch_bytes(long M, int ny, int nx);
 // synchronous on s; scratch: toeplitz_scratch_bytes(M, ny, nx) bytes of device memory
-hipError_t build_toeplitz_weights(const float* traj, long M, int ny, int nx, float* w, void* scratch,
+hipError_t build_toeplitz_weights(const float* traj, long M, int ny, int nx, float* w, bool by_column, void* scratch,
                                   hipStream_t s);
 
 // FP64 compressed-sensing primal (2-D Cartesian): normal operator, power method,

@@ -118,14 +118,14 @@ __global__ void k_dft_matrix(z64* __restrict__ F, int G) {
 }
 
 // w[row(ky)][kx] = Re(Kh[ky][kx]) * scale; row: the even ky in order, then the odd
-// ones (the column pass transforms them separately)
+// ones (the column pass transforms them separately); by_column: w[kx][ky]
 __global__ void k_real_weights(const z64* __restrict__ kh, float* __restrict__ w, int Gy, int Gx,
-                               double scale) {
+                               double scale, int by_column) {
   const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= (long)Gy * Gx) return;
   const int ky = (int)(i / Gx), kx = (int)(i % Gx);
   const int row = (ky & 1) * (Gy / 2) + ky / 2;
-  w[(size_t)row * Gx + kx] = (float)(kh[i].x * scale);
+  w[by_column ? (size_t)kx * Gy + ky : (size_t)row * Gx + kx] = (float)(kh[i].x * scale);
 }
 
 static hipError_t zgemm64(const double2* A, const double2* B, double2* C, int Mr, int Nc, int Kd, int transA,
@@ -173,7 +173,7 @@ size_t toeplitz_scratch_bytes(long M, int ny, int nx) { return ToeplitzScratch(M
     if (e_ != hipSuccess) return e_; \
   } while (0)
 
-hipError_t build_toeplitz_weights(const float* traj, long M, int ny, int nx, float* w, void* scratch,
+hipError_t build_toeplitz_weights(const float* traj, long M, int ny, int nx, float* w, bool by_column, void* scratch,
                                   hipStream_t s) {
   const int Dy = 2 * ny - 1, Dx = 2 * nx - 1, Gy = 2 * ny, Gx = 2 * nx;
   const ToeplitzScratch L(M, ny, nx);
@@ -210,7 +210,7 @@ hipError_t build_toeplitz_weights(const float* traj, long M, int ny, int nx, flo
   TZ_CHECK(zgemm64(Fy, kg, t1, Gy, Gx, Gy, 0, 1, s));
   TZ_CHECK(zgemm64(t1, Fx, kh, Gy, Gx, Gx, 0, 1, s));
   hipLaunchKernelGGL(k_real_weights, dim3((unsigned)((ng + 255) / 256)), dim3(256), 0, s, kh, w, Gy, Gx,
-                     1.0 / ((double)Gy * Gx));
+                     1.0 / ((double)Gy * Gx), by_column ? 1 : 0);
   TZ_CHECK(hipGetLastError());
   return hipStreamSynchronize(s);
 }
