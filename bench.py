@@ -1323,7 +1323,7 @@ def main():
     roofline = {
         "bound": "alu", "achieved": round(achieved_tf, 2), "peak": PEAK_FP32_TFLOPS,
         "unit": "TFLOP/s", "frac": round(achieved_tf / PEAK_FP32_TFLOPS, 4), "traffic": traffic,
-        "kernel": "k_cart1d<TwoStep<20,16>, C1_ITER>", "avg_launch_us": round(avg_s * 1e6, 2),
+        "kernel": "k_cart1d_split<ColPlan<16,10>, 2, C1_ITER>", "avg_launch_us": round(avg_s * 1e6, 2),
         "flops_per_launch": flops, "alg_bytes_per_launch": bytes_alg,
         "hbm_GBs_alg": round(bytes_alg / avg_s / 1e9, 1),
     }

@@ -33,8 +33,9 @@
 //
 // Bound by the vector ALU (FP32, not packed) with the CG fields' traffic close
 // behind: 320 x 320 x 15 coils, R = 2 + 24 calibration lines, K = 256, one CG
-// iteration 0.54 ms (VALU 82 % busy; the eight fields read and written, 1.7 GB,
-// take 0.36 ms at the copy rate) against 0.79 ms unsplit.
+// iteration 0.55 ms (VALU instructions issued in 92 % of the cycles; the eight
+// fields read and written, 1.7 GB, take 0.36 ms at the copy rate) against 0.79 ms
+// unsplit.
 #pragma once
 
 #include <type_traits>

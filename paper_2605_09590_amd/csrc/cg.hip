@@ -148,7 +148,8 @@ __global__ __launch_bounds__(64 * kAccumSlices) void k_accum(AccumArgs a) {
   if (a.sumsq) a.sumsq[vox] += ss;
 }
 
-// sixteen slices while the pixels alone give less than two wavefronts a SIMD, else four
+// four slices, or sixteen where four would give less than two wavefronts a SIMD (1024
+// SIMDs: fewer than 512 groups of 64 pixels)
 template <bool COL>
 static hipError_t accum(const AccumArgs& a, hipStream_t s) {
   const int groups = (a.ny * a.nx + 63) / 64;
