@@ -12,6 +12,7 @@
 // forward transform followed by an inverse one stays in layout B's registers.
 #pragma once
 
+#include <atomic>
 #include <type_traits>
 
 #include "fft.h"
@@ -124,10 +125,18 @@ static hipError_t with_col(int n, F&& f) {
   }
 }
 
-// dynamic LDS above 64 KiB has to be allowed per kernel (once per process,
-// thread-safe initialisation at the call)
-inline hipError_t allow_lds(const void* kernel) {
-  return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+// Dynamic LDS above 64 KiB has to be allowed per kernel and device: allowed, one per
+// kernel, has a bit for each device where it has been (the first 64; others ask again)
+inline hipError_t allow_lds(const void* kernel, size_t bytes, std::atomic<uint64_t>& allowed) {
+  if (bytes <= 64 * 1024) return hipSuccess;
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  const uint64_t bit = dev < 64 ? (uint64_t)1 << dev : 0;
+  if (allowed.load(std::memory_order_acquire) & bit) return hipSuccess;
+  e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+  if (e == hipSuccess) allowed.fetch_or(bit, std::memory_order_release);
+  return e;
 }
 
 }  // namespace pico

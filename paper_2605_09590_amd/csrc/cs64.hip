@@ -179,8 +179,9 @@ template <bool PAIR>
 hipError_t cols64(const Cs64& o, long planes, hipStream_t s) {
   return with_line64(o.ny, [&](auto cp) {
     using CP = decltype(cp);
-    static const hipError_t attr = allow_lds((const void*)k_cols64<CP, PAIR>);
-    if (attr != hipSuccess) return attr;
+    static std::atomic<uint64_t> allowed{0};
+    const hipError_t e = allow_lds((const void*)k_cols64<CP, PAIR>, CP::LDS, allowed);
+    if (e != hipSuccess) return e;
     const dim3 grid(strip_grid(planes * (o.nx / CP::ST))), block(CP::THREADS);
     hipLaunchKernelGGL((k_cols64<CP, PAIR>), grid, block, CP::LDS, s, o.U, o.mask, planes, o.nx, o.twy);
     return hipGetLastError();

@@ -95,8 +95,9 @@ __global__ __launch_bounds__(CP::THREADS) void k_fft_cols(const float2* in, floa
 template <class CP, bool INV, bool CROP>
 static hipError_t fft_cols(const float2* in, float2* out, long is, long os, long planes, int ny, int Gx,
                            const float2* twt, hipStream_t s) {
-  static const hipError_t attr = allow_lds((const void*)k_fft_cols<CP, INV, CROP>);
-  if (attr != hipSuccess) return attr;
+  static std::atomic<uint64_t> allowed{0};
+  const hipError_t e = allow_lds((const void*)k_fft_cols<CP, INV, CROP>, CP::LDS, allowed);
+  if (e != hipSuccess) return e;
   const dim3 grid(strip_grid(planes * (Gx / kStrip))), block(CP::THREADS);
   hipLaunchKernelGGL((k_fft_cols<CP, INV, CROP>), grid, block, CP::LDS, s, in, out, is, os, planes, ny, Gx, twt);
   return hipGetLastError();

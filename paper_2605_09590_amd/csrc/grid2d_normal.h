@@ -743,8 +743,9 @@ static hipError_t rows_inv(int mode, const Grid2dArgs& a, hipStream_t s) {
 
 template <class CP, bool TB, bool PAD>
 static hipError_t cols(const Grid2dArgs& a, hipStream_t s) {
-  static const hipError_t attr = allow_lds((const void*)k_cols<CP, TB, PAD>);
-  if (attr != hipSuccess) return attr;
+  static std::atomic<uint64_t> allowed{0};
+  const hipError_t e = allow_lds((const void*)k_cols<CP, TB, PAD>, CP::LDS, allowed);
+  if (e != hipSuccess) return e;
   const long W = (long)(a.Gx / kStrip) * a.K * a.nc;
   hipLaunchKernelGGL((k_cols<CP, TB, PAD>), dim3(strip_grid(W)), dim3(CP::THREADS), CP::LDS, s, a);
   return hipGetLastError();
@@ -754,10 +755,8 @@ static hipError_t cols(const Grid2dArgs& a, hipStream_t s) {
 template <class CF, bool TB, bool PAD>
 static hipError_t cols_staged(const Grid2dArgs& a, hipStream_t s) {
   constexpr int NC = 256 / CF::L, NY = PAD ? CF::N / 2 : CF::N;
-  static const hipError_t attr = allow_lds((const void*)k_cols_staged<CF, TB, PAD>);
-  if (attr != hipSuccess) return attr;
   constexpr size_t lds = std::max((size_t)NY * (NC + 1), (size_t)NC * CF::SPAN) * sizeof(float2);
-  static_assert(lds <= 160 * 1024, "fits the LDS");
+  static_assert(lds <= 64 * 1024, "without leave");
   const long W = (long)(a.Gx / NC) * a.K * a.nc;
   hipLaunchKernelGGL((k_cols_staged<CF, TB, PAD>), dim3(strip_grid(W)), dim3(256), lds, s, a);
   return hipGetLastError();
