@@ -16,8 +16,29 @@ bool cart1d_supported(int ny) {
   }
 }
 
+// Launches with fewer split wavefronts than SIMDs (1024) whose class to transform makes
+// them slower than whole columns, which put more lanes on a probe: one wavefront's
+// time counts then.  Maps of 20 CG iterations, 12 coils, R = 2 (384*: R = 4, S = 1) + 24
+// lines, 128 columns, us, whole columns / split, K in brackets:
+// - a last wavefront at most half full: 64 [1] 404 / 433, [4] 416 / 440, [5] 413 / 402; 192
+//   [2] 636 / 679, [3] 634 / 604; 256 (S = 1) [2] 768 / 883, [3] 774 / 754, [6] 780 / 865; 288
+//   [2] 829 / 879, [3] 834 / 782; 320 [2] 790 / 891, [4] 800 / 793, [5] 805 / 859; 384 [2]
+//   860 / 970, [4] 870 / 864, [5] 905 / 936;
+// - any: 128 [8] 559 / 573, [32] 614 / 639, [48: 768 wavefronts] 714 / 696; 160 [12] 647 / 673,
+//   [16] 655 / 690, [48: 1024] 842 / 786; 384* [2] 859 / 906, [16: 1024] 1042 / 1051, [32] 1293 /
+//   1272; 512 [1] 526 / 1273, [16] 812 / 1176, [28: 896] 1361 / 1385, [40] 1564 / 1529.
+static bool whole_columns(const Cart1dArgs& a) {
+  if (a.rho < 0 || a.split == 3 || a.ny == 96) return false;   // 96: 937 / 532 at [4]
+  const int probes = 64 / split_lanes(a.split, a.ny), last = a.K % probes;
+  const long waves = (long)a.nx * ((a.K + probes - 1) / probes);
+  if (waves >= 1024) return false;
+  if (last > 0 && 2 * last <= probes) return true;
+  if (a.split == 1) return a.ny == 384;
+  return a.ny == 160 || a.ny == 512 || (a.ny == 128 && waves <= 512);
+}
+
 hipError_t launch_cart1d(int mode, const Cart1dArgs& a, hipStream_t s) {
-  if (mode != C1_PMR_RHS) {
+  if (mode != C1_PMR_RHS && !((a.split > 1 || unsplit_in_split_kernel(a.ny)) && whole_columns(a))) {
     if (a.split == 2) return launch_cart1d_split2(mode, a, s);
     if (a.split == 3) return launch_cart1d_split3(mode, a, s);
     if (unsplit_in_split_kernel(a.ny)) return launch_cart1d_split1(mode, a, s);

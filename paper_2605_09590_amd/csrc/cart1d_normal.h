@@ -2,7 +2,8 @@
 // pseudo-replica right-hand side (kernel templates; complex64 and bfloat16 map
 // storage are instantiated in translation units of their own).  Masks that leave
 // a residue class of the frequencies full or empty take the split kernel instead
-// (cart1d_split.h), which also has the better plans for some unsplit lengths.
+// (cart1d_split.h), which also has the better plans for some unsplit lengths, but
+// for launches of few probes.
 //
 // With a phase-encode mask that is constant along kx, the whitened normal
 // operator M = sum_c S_c^H F^H P F S_c (Sec. 2.1, Eqs. (3), (6)) is block
@@ -185,9 +186,9 @@ __global__ __launch_bounds__(64) void k_cart1d(Cart1dArgs a) {
 
   typename CF::Tw tw;
   CF::load_tw(tw, a.twt, lane);
-  // maps that carry W_N^{rho y} (split form, complex64): the right-hand side's noise
-  // goes into the transform rho lines lower, which gives the sum the same factor
-  const int shift = MODE == C1_PMR_RHS && !BF && a.rho > 0 ? a.rho : 0;
+  // maps that carry W_N^{rho y} (split form, complex64): every line of the transforms
+  // lies rho lower (the right-hand side's noise too, which gives the sum that factor)
+  const int shift = !BF && a.rho > 0 ? a.rho : 0;
   MaskLines<CF> mk;
   mk.load(a.maskw, lane, shift);
 
@@ -344,7 +345,7 @@ template <class CF, bool BF>
 static hipError_t launch_plan(int mode, const Cart1dArgs& a, hipStream_t s) {
   constexpr int G = 64 / CF::L;
   dim3 grid((a.K + G - 1) / G, a.nx), block(64);
-  if constexpr (unsplit_in_split_kernel(CF::N)) {   // the normal operator runs in cart1d_split.h
+  if constexpr (CF::N == 96) {   // the normal operator always runs in cart1d_split.h
     if (mode != C1_PMR_RHS) return hipErrorInvalidValue;
     hipLaunchKernelGGL((k_cart1d<CF, C1_PMR_RHS, BF>), grid, block, 0, s, a);
     return hipGetLastError();

@@ -380,6 +380,7 @@ static hipError_t split_modes(int mode, const Cart1dArgs& a, hipStream_t s) {
 
 template <int S, class CP>
 static hipError_t split_launch(int mode, const Cart1dArgs& a, hipStream_t s) {
+  static_assert(CP::LA == split_lanes(S, S * CP::N), "the plan of this length");
   constexpr int NW = kBlockWaves<CP, S>;
   if (a.full[0].x == 0.0) return split_modes<S, CP, 0, true>(mode, a, s);
   const bool share = a.K > kFoldProbes<CP> * (NW - 1);   // a workgroup's wavefronts all have probes

@@ -324,6 +324,12 @@ hipError_t launch_cart1d_split3(int mode, const Cart1dArgs& a, hipStream_t s);
 // -> 1.08, 384 2.13 -> 1.92; the others 64 0.42 -> 0.44, 128 0.69 -> 0.71, 160
 // 0.81 -> 0.83, 192 and 288 equal, 320 1.50 -> 1.59, 512 2.23 -> 2.70)
 constexpr bool unsplit_in_split_kernel(int ny) { return ny == 96 || ny == 256 || ny == 384; }
+// lanes per probe of the split kernel's plans
+constexpr int split_lanes(int split, int ny) {
+  if (split == 1) return ny == 96 ? 12 : ny == 256 ? 16 : 24;
+  if (split == 3) return ny <= 192 ? 8 : ny == 288 ? 12 : 16;
+  return ny <= 128 ? 8 : ny == 160 ? 10 : ny == 192 || ny == 288 ? 12 : 16;
+}
 // split of a phase-encode mask's frequencies into classes k = rho (mod split):
 // the fully and the partly sampled ones (at most one of these)
 struct Fold {
