@@ -806,22 +806,33 @@ static hipError_t grid_passes(int mode, const Grid2dArgs& a, hipStream_t s) {
 // K = 128) 13.7 / 11.2, 288 x 288 masked (20, K = 64) 15.8 / 14.5; 1706 wavefronts / 3413:
 // 160 x 160 spiral (8 coils) 7.2 / 7.5 ms, 320 x 320 masked (8) 13.3 / 13.9; sets of
 // 64 MiB are slower than one pass (20.8, 11.6, 17.2, 17.0 ms).
-inline int grid_chunk(int K, int ny, int group, size_t plane) {
+// One pass after all, maps of 10 CG iterations, ms, one pass / sets:
+// - planes of up to 256 MiB whose rows are one round: sets only halve the launches (spiral
+//   160 x 128, 17 coils, K = 43: 2.32 / 2.72, K = 50, 265 MiB: 2.85 / 2.82; 256 x 256, 16, 14:
+//   2.19 / 2.59; masked 192 x 192, 24, 33: 2.13 / 2.40);
+// - unpadded lines of 320 points and more that need 1.25 times the rounds in sets (320 x
+//   320, 32 coils, K = 32: 9.65 / 10.12; 384, 32, 24: 11.15 / 11.71; 576, 24, 14: 10.96 /
+//   12.92; 640, 12, 22: 10.84 / 11.60; 768, 32, 6: 11.17 / 12.46; with fewer rounds 384, 24,
+//   24: 8.46 / 8.06; shorter lines 256, 24, 40: 5.37 / 4.83; padded 256, 32, 24: 8.23 / 6.95
+//   and 320, 32, 14: 9.56 / 8.88).
+inline int grid_chunk(int K, int ny, int group, size_t plane, int line, bool pad) {
   const size_t most = 216u << 20, least = 96u << 20;
   if (K * plane <= most) return K;
+  const auto rounds = [&](long k) { return (k * ny + group * 2048L - 1) / (group * 2048L); };
+  if (K * plane <= (size_t)256 << 20 && rounds(K) == 1) return K;
   const size_t fit = std::max<size_t>(1, most / plane);
   long best = -1;
   int set = (int)fit;
   for (long n = (K + fit - 1) / fit; n <= K; ++n) {
     const long c = (K + n - 1) / n, full = K / c, rest = K - full * c;
     if (best >= 0 && c * plane < least) break;
-    const auto rounds = [&](long k) { return (k * ny + group * 2048L - 1) / (group * 2048L); };
     const long all = full * rounds(c) + rounds(rest);
     if (best < 0 || all <= best) {
       best = all;
       set = (int)c;
     }
   }
+  if (!pad && line >= 320 && 4 * best >= 5 * rounds(K)) return K;
   return set;
 }
 
@@ -830,7 +841,7 @@ static hipError_t grid_normal(int mode, const Grid2dArgs& all, hipStream_t s) {
   const size_t plane = (size_t)all.nc * all.ny * all.Gx * (ST == 2 ? 4 : 8), n = (size_t)all.ny * all.nx;
   int chunk = 0;
   const hipError_t known = with_line(all.Gx, [&](auto cf) {
-    chunk = grid_chunk(all.K, all.ny, 64 / decltype(cf)::L, plane);
+    chunk = grid_chunk(all.K, all.ny, 64 / decltype(cf)::L, plane, all.Gx, all.Gy == 2 * all.ny);
     return hipSuccess;
   });
   if (known != hipSuccess) return known;
