@@ -52,14 +52,18 @@ struct MaskLines {
   float w[kRegs ? CF::VB : 1];
   uint32_t bits = 0;
   // value r of the lane is line posB + shift (mod N)
-  __device__ __forceinline__ void load(const float* __restrict__ maskw, int lane, int shift = 0) {
+  template <bool SHIFT>
+  __device__ __forceinline__ void load(const float* __restrict__ maskw, int lane, int shift) {
     const bool inB = CF::inB(lane);
 #pragma unroll
     for (int r = 0; r < CF::VB; ++r) {
       // one batch of loads from in-bounds indices, zeroed by a factor (a
       // load under the lane condition gets a branch and a wait of its own)
-      int k = (inB ? CF::posB(lane, r) : 0) + shift;
-      k -= k >= CF::N ? CF::N : 0;
+      int k = inB ? CF::posB(lane, r) : 0;
+      if constexpr (SHIFT) {
+        k += shift;
+        k -= k >= CF::N ? CF::N : 0;
+      }
       const float m = maskw[k] * (inB ? 1.f : 0.f);
       if constexpr (kRegs) w[r] = m;
       bits |= (m != 0.f ? 1u : 0u) << r;
@@ -165,7 +169,9 @@ __device__ __forceinline__ double group_reduce(const double (&v)[J], double* red
   return s;
 }
 
-template <class CF, int MODE, bool BF>
+// SHIFT: maps that carry W_N^{rho y} (split form, complex64): every line of the transforms
+// lies rho lower (the right-hand side's noise too, which gives the sum that factor)
+template <class CF, int MODE, bool BF, bool SHIFT>
 __global__ __launch_bounds__(64) void k_cart1d(Cart1dArgs a) {
   constexpr int N = CF::N, L = CF::L, G = 64 / L, NG = (64 + L - 1) / L;
   constexpr int VA = CF::VA, VB = CF::VB;
@@ -186,11 +192,9 @@ __global__ __launch_bounds__(64) void k_cart1d(Cart1dArgs a) {
 
   typename CF::Tw tw;
   CF::load_tw(tw, a.twt, lane);
-  // maps that carry W_N^{rho y} (split form, complex64): every line of the transforms
-  // lies rho lower (the right-hand side's noise too, which gives the sum that factor)
-  const int shift = !BF && a.rho > 0 ? a.rho : 0;
+  const int shift = SHIFT ? a.rho : 0;
   MaskLines<CF> mk;
-  mk.load(a.maskw, lane, shift);
+  mk.template load<SHIFT>(a.maskw, lane, shift);
 
   const size_t base = ((size_t)kk * a.nx + col) * N;
   const MS mcol = MS::of(a) + (size_t)col * a.nc * N;
@@ -341,24 +345,32 @@ __global__ __launch_bounds__(64) void k_cart1d(Cart1dArgs a) {
 }
 
 // ------------------------------------------------------------ dispatch
-template <class CF, bool BF>
-static hipError_t launch_plan(int mode, const Cart1dArgs& a, hipStream_t s) {
+template <class CF, bool BF, bool SHIFT>
+static hipError_t launch_modes(int mode, const Cart1dArgs& a, hipStream_t s) {
   constexpr int G = 64 / CF::L;
   dim3 grid((a.K + G - 1) / G, a.nx), block(64);
   if constexpr (CF::N == 96) {   // the normal operator always runs in cart1d_split.h
     if (mode != C1_PMR_RHS) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_cart1d<CF, C1_PMR_RHS, BF>), grid, block, 0, s, a);
+    hipLaunchKernelGGL((k_cart1d<CF, C1_PMR_RHS, BF, SHIFT>), grid, block, 0, s, a);
     return hipGetLastError();
   }
   switch (mode) {
-    case C1_FIRST_PROBE: hipLaunchKernelGGL((k_cart1d<CF, C1_FIRST_PROBE, BF>), grid, block, 0, s, a); break;
-    case C1_FIRST_BUF: hipLaunchKernelGGL((k_cart1d<CF, C1_FIRST_BUF, BF>), grid, block, 0, s, a); break;
-    case C1_ITER: hipLaunchKernelGGL((k_cart1d<CF, C1_ITER, BF>), grid, block, 0, s, a); break;
-    case C1_APPLY: hipLaunchKernelGGL((k_cart1d<CF, C1_APPLY, BF>), grid, block, 0, s, a); break;
-    case C1_PMR_RHS: hipLaunchKernelGGL((k_cart1d<CF, C1_PMR_RHS, BF>), grid, block, 0, s, a); break;
+    case C1_FIRST_PROBE: hipLaunchKernelGGL((k_cart1d<CF, C1_FIRST_PROBE, BF, SHIFT>), grid, block, 0, s, a); break;
+    case C1_FIRST_BUF: hipLaunchKernelGGL((k_cart1d<CF, C1_FIRST_BUF, BF, SHIFT>), grid, block, 0, s, a); break;
+    case C1_ITER: hipLaunchKernelGGL((k_cart1d<CF, C1_ITER, BF, SHIFT>), grid, block, 0, s, a); break;
+    case C1_APPLY: hipLaunchKernelGGL((k_cart1d<CF, C1_APPLY, BF, SHIFT>), grid, block, 0, s, a); break;
+    case C1_PMR_RHS: hipLaunchKernelGGL((k_cart1d<CF, C1_PMR_RHS, BF, SHIFT>), grid, block, 0, s, a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
+}
+
+template <class CF, bool BF>
+static hipError_t launch_plan(int mode, const Cart1dArgs& a, hipStream_t s) {
+  if constexpr (!BF) {   // packed maps carry no phase
+    if (a.rho > 0) return launch_modes<CF, BF, true>(mode, a, s);
+  }
+  return launch_modes<CF, BF, false>(mode, a, s);
 }
 
 // Column-FFT layouts per line length.  Stockham plans keep N/T values on T
